@@ -1,0 +1,382 @@
+"""The work this framework is measured on: its public calls over the sizes its users run.
+
+A case is one call (or one training step) of the Python binding.  ``listed()`` names
+twelve, from a single small scan to the multistatic array at full size; ``draw`` gives
+more of the same kinds, their sizes spread over the same ranges.  Inputs are echoes of
+random point scatterers with noise, made here in 64 bits; ``exact`` evaluates the same
+definitions by direct sums in 64 bits.
+"""
+from __future__ import annotations
+
+import math
+from types import SimpleNamespace
+
+import torch
+
+import paper_2109_02842_amd as pr
+from paper_2109_02842_amd import autograd as pr_autograd
+
+C0 = 299_792_458.0
+D_MONO = C0 / (2 * 34e9)     # half a wavelength at 34 GHz: transceivers
+D_MULTI = C0 / 34e9          # a wavelength: multistatic receivers
+SCATTERERS = 24              # point targets behind every echo cube
+EXACT_LIMIT = 4e11           # phase factors a direct sum may take (about 10 s on the GPU)
+
+
+def _case(name, kind, mode="mono", chords=5, elem=64, tx=0, radius=0.6, scan=256, step=0.004, freq=64,
+          nx=200, ny=200, pitch=0.003, precision="fp32", mfma=0, prepared=True, **more):
+    c = dict(kind=kind, mode=mode, chords=chords, elem=elem, tx=tx, radius=radius, scan=scan, step=step,
+             freq=freq, nx=nx, ny=ny, pitch=pitch, precision=precision, mfma=mfma, prepared=prepared)
+    c.update(more)
+    if name is not None:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # the smallest scan that is reconstructed in earnest (3 x 16 transceivers, 24 scan positions, 16
+        # frequencies, 32 x 32 pixels), repeated with a kept plan: launches and latency
+        _case("small_scan", "recon", chords=3, elem=16, radius=0.5, scan=24, step=0.005, freq=16, nx=32, ny=32,
+              pitch=0.3 / 32),
+        # a single multistatic scan with the paper's sampling (51 frequencies, 1 m circle, 10.2 mm receivers),
+        # reconstructed once by the plain call: plan, tables and image each time
+        _case("small_multi_plain", "recon", mode="multi", chords=3, elem=20, tx=2, radius=1.0, scan=32, step=0.005,
+              freq=51, nx=32, ny=32, pitch=0.2 / 32, prepared=False),
+        # the standard monostatic scan, 320 channels, 64 frequencies, 200 x 200 x 256 voxels, plan kept
+        _case("mono_fp32", "recon"),
+        # its two matrix-core modes that a caller asks for: one FP16 product, and split BF16
+        _case("mono_fp16_1pass", "recon", precision="fp16", mfma=2),
+        _case("mono_bf16_split", "recon", precision="bf16", mfma=1),
+        # an odd scan (389 positions, a prime; 100 frequencies, an image that fits no tile), plain call
+        _case("ragged_fp32", "recon", chords=4, elem=45, scan=389, freq=100, nx=131, ny=97, pitch=0.6 / 128,
+              prepared=False),
+        # the multistatic array at full size: 896 channels, 512 scan positions, 128 frequencies, 256 x 256 x 512
+        _case("multi_fp32", "recon", mode="multi", chords=7, elem=32, tx=4, radius=0.8, scan=512, step=0.003,
+              freq=128, nx=256, ny=256, pitch=0.6 / 256),
+        # a queue of scans of uneven sizes served by one batch call
+        _case("batch_uneven", "batch", scans=8, first=50, nx=128, ny=128, pitch=0.6 / 128),
+        # the adjoint (image to echo): the echo model of least-squares refinement, at the standard size
+        _case("adjoint_fp32", "adjoint"),
+        # one training step through the autograd function: image, loss, gradient of the echo, odd sizes
+        _case("train_step", "train", chords=3, elem=40, scan=150, freq=48, nx=90, ny=101, pitch=0.0035),
+        # echo simulation of a scene of 2000 scatterers at the standard size
+        _case("simulate", "simulate", scat=2000),
+        # brute-force back-projection of a slab of four planes, the comparison method
+        _case("direct_bp", "bp", chords=5, elem=32, scan=128, freq=64, nx=64, ny=64, pitch=0.005, planes=4),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case: a kind by how often it is used, sizes over the listed range (scans 24-512, frequencies
+    16-128, images 32-256 pixels wide, 3-7 chords of 16-64 elements)."""
+    kind = rng.choices(["recon", "recon_1pass", "recon_split", "batch", "adjoint", "train", "simulate", "bp"],
+                       [8, 2, 2, 1, 2, 2, 1, 1])[0]
+    if kind == "batch":
+        n = rng.randint(96, 144)
+        return _case(None, "batch", scans=rng.randint(2, 8), first=rng.randint(100, 10**6), nx=n,
+                     ny=rng.randint(96, 144), pitch=0.6 / n)
+    mode = "multi" if kind != "bp" and rng.random() < 0.3 else "mono"
+    chords = rng.randint(3, 7)
+    elem = rng.randint(16, 32) if mode == "multi" else rng.randint(16, 64)
+    tx = rng.choice([2, 4]) if mode == "multi" else 0
+    step = rng.choice([0.003, 0.004, 0.005])
+    scan, freq = _log_int(rng, 24, 512), _log_int(rng, 16, 128)
+    nx, ny = _log_int(rng, 32, 256), _log_int(rng, 32, 256)
+    pitch = rng.uniform(0.0022, 0.0095)
+    more = {}
+    if kind in ("recon_1pass", "recon_split"):
+        # the matrix-core modes take fine pixels
+        scan, pitch = _log_int(rng, 96, 512), rng.uniform(0.0022, 0.0032)
+        more = dict(precision="fp16", mfma=2) if kind == "recon_1pass" else dict(precision=rng.choice(["bf16", "fp16"]), mfma=1)
+    elif kind in ("adjoint", "train"):
+        scan, pitch = _log_int(rng, 64, 400), rng.uniform(0.0022, 0.004)
+    elif kind == "simulate":
+        more = dict(scat=_log_int(rng, 50, 2000))
+    elif kind == "bp":
+        chords, elem, scan, nx, ny = rng.randint(3, 5), rng.randint(16, 32), _log_int(rng, 24, 128), \
+            _log_int(rng, 24, 64), _log_int(rng, 24, 64)
+        more = dict(planes=rng.randint(1, 6))
+    pitch = min(pitch, 0.6 / max(nx, ny))   # images of at most 0.6 m
+    radius = rng.choice([0.6, 0.8, 1.0])
+    if kind.startswith("recon"):
+        kind, more["prepared"] = "recon", rng.random() < 0.6
+    return _case(None, kind, mode=mode, chords=chords, elem=elem, tx=tx, radius=radius, scan=scan, step=step,
+                 freq=freq, nx=nx, ny=ny, pitch=pitch, **more)
+
+
+# ---------------------------------------------------------------- descriptions
+def _scans(case):
+    """The (array, grid) descriptions of a case: one, or those of a batch."""
+    if case["kind"] != "batch":
+        multi = case["mode"] == "multi"
+        return [(_array(case["mode"], case["chords"], case["radius"], case["elem"], case["tx"],
+                        (0.0102 if case["radius"] == 1.0 else D_MULTI) if multi else D_MONO,
+                        case["scan"], case["step"], case["freq"]), _grid(case))]
+    import random
+    out = []
+    for s in range(case["scans"]):
+        r = random.Random(case["first"] + s)
+        out.append((_array("mono", r.randint(3, 7), 0.6, r.randint(32, 64), 0, D_MONO, r.randint(128, 512), 0.004,
+                           r.randint(32, 128)), _grid(case)))
+    return out
+
+
+def _array(mode, chords, radius, elem, tx, spacing, scan, step, freq):
+    return SimpleNamespace(mode=mode, n_chords=chords, radius=radius, n_elem=elem, n_tx=tx, spacing=spacing,
+                           n_scan=scan, scan_step=step, n_freq=freq, f_start=26e9, f_stop=34e9)
+
+
+def _grid(case):
+    nx, ny, d = case["nx"], case["ny"], case["pitch"]
+    return SimpleNamespace(nx=nx, ny=ny, x0=-(nx - 1) * d / 2, y0=-(ny - 1) * d / 2, dx=d, dy=d)
+
+
+def _channels(a):
+    return a.n_chords * a.n_elem * (a.n_tx or 1)
+
+
+def _opts(case):
+    return dict(precision=case["precision"], mfma_backprojection=case["mfma"])
+
+
+def _device():
+    return "cuda" if torch.cuda.is_available() else "cpu"
+
+
+# ---------------------------------------------------------------------- inputs
+def _geometry(a):
+    """Transmit and receive positions (n_ch, 2), scan heights and wavenumbers, float64."""
+    length = a.n_elem * a.spacing
+    alpha = 2 * math.asin(length / (2 * a.radius))
+    offs = [(j + 0.5) * a.spacing - length / 2 for j in range(a.n_elem)]
+    toffs = {0: [], 2: [-length / 2, length / 2],
+             4: [-length / 2, -length / 2 + a.spacing / 2, length / 2 - a.spacing / 2, length / 2]}[a.n_tx]
+    tx, rx = [], []
+    for i in range(a.n_chords):
+        phi = -math.pi / 2 + (i - (a.n_chords - 1) / 2) * alpha
+        p = [(a.radius * math.cos(t), a.radius * math.sin(t)) for t in (phi - alpha / 2, phi + alpha / 2)]
+        mx, my = (p[0][0] + p[1][0]) / 2, (p[0][1] + p[1][1]) / 2
+        ux, uy = (p[1][0] - p[0][0]) / length, (p[1][1] - p[0][1]) / length
+        elems = [(mx + o * ux, my + o * uy) for o in offs]
+        if a.n_tx:
+            for o in toffs:
+                tx += [(mx + o * ux, my + o * uy)] * a.n_elem
+                rx += elems
+        else:
+            tx += elems
+            rx += elems
+    d = dict(dtype=torch.float64, device=_device())
+    z = (torch.arange(a.n_scan, **d) - (a.n_scan - 1) / 2) * a.scan_step
+    k = 2 * math.pi / C0 * torch.linspace(a.f_start, a.f_stop, a.n_freq, **d)
+    return torch.tensor(tx, **d), torch.tensor(rx, **d), z, k
+
+
+def _scene(a, grid, n, gen):
+    """n scatterers on a shell inside the image: positions (n, 3) and reflectivities, float64."""
+    v = torch.randn(n, 3, dtype=torch.float64, generator=gen)
+    v /= v.norm(dim=1, keepdim=True)
+    half = torch.tensor([0.42 * grid.nx * grid.dx, 0.33 * grid.ny * grid.dy, 0.45 * a.n_scan * a.scan_step])
+    refl = torch.randn(n, 2, dtype=torch.float64, generator=gen) / math.sqrt(2)
+    return (v * half).to(_device()), torch.view_as_complex(refl).to(_device())
+
+
+def _echo64(a, xyz, refl):
+    """s[c][m][f] = sum_p sigma_p exp(-j k_f (R_T + R_R)), complex128."""
+    tx, rx, z, k = _geometry(a)
+    n_ch, n_p = tx.shape[0], xyz.shape[0]
+    out = torch.empty(n_ch, a.n_scan, a.n_freq, dtype=torch.complex128, device=tx.device)
+    step = max(1, int(4e7 // (a.n_scan * a.n_freq * n_p)))
+    dz2 = (z[:, None] - xyz[None, :, 2]) ** 2
+    for c in range(0, n_ch, step):
+        path = sum(torch.sqrt(((t[c:c + step, None, :] - xyz[None, :, :2]) ** 2).sum(-1)[:, None, :] + dz2)
+                   for t in (tx, rx))
+        out[c:c + step] = torch.polar(torch.ones((), dtype=torch.float64, device=tx.device).expand(
+            path.shape[0], a.n_scan, a.n_freq, n_p), -path[:, :, None, :] * k[None, None, :, None]) @ refl
+    return out
+
+
+def _gen(seed, k=0):
+    return torch.Generator().manual_seed(1_000_003 * int(seed) + k)
+
+
+def _echo(a, grid, seed, k=0):
+    """A complex64 echo cube: point scatterers and white noise 30 dB below them."""
+    gen = _gen(seed, k)
+    s = _echo64(a, *_scene(a, grid, SCATTERERS, gen))
+    g = torch.Generator(device=s.device).manual_seed(int(torch.randint(1 << 40, (1,), generator=gen)))
+    noise = torch.view_as_complex(torch.randn(*s.shape, 2, dtype=torch.float32, device=s.device, generator=g))
+    return (s + noise * (s.abs().square().mean().sqrt() * (10 ** -1.5 / math.sqrt(2)))).to(torch.complex64)
+
+
+def _image(a, grid, seed, k=0):
+    """A complex64 image of white noise: every k_z and every direction carries energy."""
+    g = torch.Generator(device=_device()).manual_seed(1_000_003 * int(seed) + 77 + k)
+    x = torch.randn(a.n_scan, grid.ny, grid.nx, 2, dtype=torch.float32, device=_device(), generator=g)
+    return torch.view_as_complex(x)
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    scans = _scans(case)
+    st = SimpleNamespace(kind=kind, opts=_opts(case), ws=None, out=None)
+    if kind == "batch":
+        geoms, grids = [pr.make_geometry(a) for a, _ in scans], [g for _, g in scans]
+        st.batch = pr.HybridBatch(geoms, grids)
+        st.ws = pr.hybrid_batch_prepare(st.batch, pr.workspace(st.batch.workspace_bytes))
+        st.echoes = [_echo(a, g, seed, k) for k, (a, g) in enumerate(scans)]
+        st.outs = [torch.empty(st.batch.image_shape(i), dtype=torch.complex64, device="cuda") for i in range(len(scans))]
+        return st
+    (a, st.grid), = scans
+    st.geom = pr.make_geometry(a)
+    if kind == "simulate":
+        st.xyz, st.refl = _scene(a, st.grid, case["scat"], _gen(seed))
+        st.out = torch.empty(st.geom.echo_shape, dtype=torch.complex64, device="cuda")
+        return st
+    image_shape = (a.n_scan, st.grid.ny, st.grid.nx)
+    if kind == "adjoint":
+        st.image = _image(a, st.grid, seed)
+        st.ws = pr.workspace(pr.hybrid_workspace_bytes(st.geom, st.grid, **st.opts))
+        st.out = torch.empty(st.geom.echo_shape, dtype=torch.complex64, device="cuda")
+        return st
+    st.echo = _echo(a, st.grid, seed)
+    if kind == "train":
+        st.echo.requires_grad_(True)
+        st.target = _image(a, st.grid, seed)
+    elif kind == "bp":
+        st.iz0, st.nz = max(0, a.n_scan // 2 - case["planes"] // 2), case["planes"]
+        st.ws = pr.workspace(pr.bp_workspace_bytes(st.geom, st.grid, st.nz))
+        st.out = torch.empty((st.nz,) + image_shape[1:], dtype=torch.complex64, device="cuda")
+    elif case["prepared"]:
+        st.ws = pr.hybrid_prepare(st.geom, st.grid, **st.opts)
+        st.out = torch.empty(image_shape, dtype=torch.complex64, device="cuda")
+    return st
+
+
+def run(st):
+    kind = st.kind
+    if kind == "recon":
+        if st.ws is None:
+            return pr.reconstruct_hybrid(st.geom, st.grid, st.echo, **st.opts)
+        return pr.reconstruct_hybrid(st.geom, st.grid, st.echo, out=st.out, ws=st.ws, prepared=True, **st.opts)
+    if kind == "batch":
+        return pr.reconstruct_hybrid_batch(st.batch, st.echoes, st.outs, st.ws, prepared=True)
+    if kind == "adjoint":
+        return pr.adjoint_hybrid(st.geom, st.grid, st.image, out=st.out, ws=st.ws, **st.opts)
+    if kind == "train":
+        st.echo.grad = None
+        image = pr_autograd.reconstruct(st.geom, st.grid, st.echo, **st.opts)
+        loss = (image - st.target).abs().square().sum()
+        loss.backward()
+        return {"image": image.detach(), "grad": st.echo.grad}
+    if kind == "simulate":
+        return pr.simulate_echo(st.geom, st.xyz, st.refl, out=st.out)
+    return pr.reconstruct_bp(st.geom, st.grid, st.echo, iz0=st.iz0, nz=st.nz, out=st.out, ws=st.ws)
+
+
+# ------------------------------------------------------------------------ work
+def work(case):
+    """Echo, image and tables once; transforms at 5 n log2 n, a four-tap interpolated sum of 24 FLOP per (k_z,
+    pixel, channel) and a range transform of 14 FLOP per (sample, ten kernel points) for the hybrid calls; 8 FLOP
+    per (voxel or scatterer, channel, scan position, frequency) and one complex multiply-add each for direct sums."""
+    nbytes = flops = 0.0
+    for a, g in _scans(case):
+        ch, z, f, p = _channels(a), a.n_scan, a.n_freq, g.nx * g.ny
+        if case["kind"] == "simulate":
+            nbytes += 8 * ch * z * f + 40 * case["scat"]
+            flops += 8.0 * case["scat"] * ch * z * f
+            continue
+        if case["kind"] == "bp":
+            nbytes += 8 * ch * z * f + 8 * p * case["planes"]
+            flops += 8.0 * p * case["planes"] * ch * z * f
+            continue
+        sides = 2 if case["kind"] == "train" else 1
+        nbytes += sides * 8 * (ch * z * f + p * z)
+        flops += sides * (5 * z * math.log2(z) * (ch * f + p) + 140.0 * ch * z * f + 24.0 * p * ch * z)
+    return {"bytes": nbytes, "flops": flops}
+
+
+# ----------------------------------------------------------------------- exact
+class _Exact:
+    """The imaging operator of one scan and its adjoint by direct sums:
+    G[kz][p] = sum_c sum_f k_f S[c][kz][f] exp(j k_rho l_c(p)), k_rho = sqrt(k^2 - kz^2 / 4), l_c = rho_T + rho_R,
+    between a transform over the scan and an inverse one over k_z."""
+
+    def __init__(self, a, g):
+        self.a, self.g = a, g
+        tx, rx, _, self.k = _geometry(a)
+        d = dict(dtype=torch.float64, device=tx.device)
+        x, y = g.x0 + g.dx * torch.arange(g.nx, **d), g.y0 + g.dy * torch.arange(g.ny, **d)
+        xy = torch.stack([x[None, :].expand(g.ny, -1), y[:, None].expand(-1, g.nx)], -1).reshape(-1, 2)
+        self.l = sum(torch.hypot(xy[:, None, 0] - t[None, :, 0], xy[:, None, 1] - t[None, :, 1]) for t in (tx, rx))
+        n = a.n_scan
+        kz = 2 * math.pi / (n * a.scan_step) * torch.tensor([i if i < (n + 1) // 2 else i - n for i in range(n)], **d)
+        arg = self.k ** 2 - kz[:, None] ** 2 / 4
+        self.valid, self.krho = arg > 0, arg.clamp(min=0).sqrt()
+        self.one = torch.ones((), **d)
+
+    def phases(self):
+        """(bins of equal k_rho, pixel slice, exp(j k_rho l) of them as (pixels, channels * frequencies))."""
+        n, n_ch, n_f = self.a.n_scan, self.l.shape[1], self.k.shape[0]
+        rows = max(1, int(1.6e8 // (n_ch * n_f)))
+        for i in range(n // 2 + 1):
+            bins = sorted({i, (n - i) % n})   # k_z and -k_z
+            for p in range(0, self.l.shape[0], rows):
+                arg = (self.l[p:p + rows, :, None] * self.krho[i]).reshape(-1, n_ch * n_f)
+                yield bins, slice(p, p + rows), torch.polar(self.one.expand(arg.shape), arg)
+
+    def image(self, echo):
+        S = torch.fft.fft(echo.to(torch.complex128), dim=1) * (self.k * self.valid)
+        G = torch.zeros(self.a.n_scan, self.l.shape[0], dtype=torch.complex128, device=S.device)
+        for bins, p, E in self.phases():
+            G[bins, p] = (E @ S[:, bins].permute(0, 2, 1).reshape(-1, len(bins)).contiguous()).T
+        return torch.fft.ifft(G, dim=0).reshape(-1, self.g.ny, self.g.nx)
+
+    def adjoint(self, image):
+        n = self.a.n_scan
+        Gt = torch.fft.fft(image.to(torch.complex128), dim=0).reshape(n, -1) / n
+        S = torch.zeros(self.l.shape[1], n, self.k.shape[0], dtype=torch.complex128, device=Gt.device)
+        for bins, p, E in self.phases():
+            part = Gt[bins, p].conj().contiguous() @ E   # conj of E^H Gt
+            S[:, bins] += part.conj().reshape(len(bins), S.shape[0], -1).permute(1, 0, 2)
+        return torch.fft.ifft(S * (self.k * self.valid), dim=1) * n
+
+
+def exact(case, seed):
+    scans, kind = _scans(case), case["kind"]
+    sums = sum(_channels(a) * a.n_scan * a.n_freq * g.nx * g.ny / 2 for a, g in scans)
+    if kind in ("recon", "adjoint", "train", "batch"):
+        if sums * (2 if kind == "train" else 1) > EXACT_LIMIT:
+            return None
+        if kind == "batch":
+            return [_Exact(a, g).image(_echo(a, g, seed, k)) for k, (a, g) in enumerate(scans)]
+        (a, g), = scans
+        op = _Exact(a, g)
+        if kind == "recon":
+            return op.image(_echo(a, g, seed))
+        if kind == "adjoint":
+            return op.adjoint(_image(a, g, seed))
+        image = op.image(_echo(a, g, seed))
+        return {"image": image, "grad": 2 * op.adjoint(image - _image(a, g, seed))}
+    (a, g), = scans
+    if kind == "simulate":
+        return _echo64(a, *_scene(a, g, case["scat"], _gen(seed)))
+    tx, rx, z, k = _geometry(a)
+    w = _echo(a, g, seed).to(torch.complex128) * k
+    op = _Exact(a, g)
+    d = dict(dtype=torch.float64, device=z.device)
+    x, y = g.x0 + g.dx * torch.arange(g.nx, **d), g.y0 + g.dy * torch.arange(g.ny, **d)
+    xy = torch.stack([x[None, :].expand(g.ny, -1), y[:, None].expand(-1, g.nx)], -1).reshape(-1, 2)
+    rho2 = [((xy[:, None, :] - t[None]) ** 2).sum(-1) for t in (tx, rx)]
+    iz0 = max(0, a.n_scan // 2 - case["planes"] // 2)
+    out = torch.zeros(case["planes"], xy.shape[0], dtype=torch.complex128, device=z.device)
+    for j in range(case["planes"]):
+        for m in range(a.n_scan):
+            path = sum(torch.sqrt(r + (z[iz0 + j] - z[m]) ** 2) for r in rho2)
+            arg = (path[:, :, None] * k).reshape(xy.shape[0], -1)
+            out[j] += torch.polar(op.one.expand(arg.shape), arg) @ w[:, m].reshape(-1)
+    return out.reshape(-1, g.ny, g.nx)
