@@ -20,7 +20,7 @@ C0 = 299_792_458.0
 D_MONO = C0 / (2 * 34e9)     # half a wavelength at 34 GHz: transceivers
 D_MULTI = C0 / 34e9          # a wavelength: multistatic receivers
 SCATTERERS = 24              # point targets behind every echo cube
-EXACT_LIMIT = 4e11           # phase factors a direct sum may take (about 10 s on the GPU)
+EXACT_LIMIT = 6e11          # phase factors a direct sum may take (about 15 s on the GPU)
 
 
 def _case(name, kind, mode="mono", chords=5, elem=64, tx=0, radius=0.6, scan=256, step=0.004, freq=64,
