@@ -23,7 +23,7 @@ int prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opt
             return fail(PL_EUNSUPPORTED, "%s: the MFMA back-projection runs only inside reconstruct_hybrid", what);
         o.mfma_backprojection = -1;
     }
-    int rc = make_plan(g, grid, (opts || stage) ? &o : nullptr, p);
+    int rc = cached_plan(g, grid, (opts || stage) ? &o : nullptr, p);
     if (rc) return rc;
     if (!ws) return fail(PL_EWORKSPACE, "%s: null workspace", what);
     if (!aligned256(ws)) return fail(PL_EWORKSPACE, "%s: workspace must be 256-byte aligned", what);
@@ -54,7 +54,7 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     clear_error();
     if (!info) return fail(PL_EINVAL, "hybrid_plan_info: null info");
     HybridPlan p;
-    const int rc = make_plan(g, grid, opts, &p);
+    const int rc = cached_plan(g, grid, opts, &p);
     if (rc) return rc;
     info->n_kz = p.n_z;
     info->n_l = p.n_l;
@@ -85,7 +85,7 @@ int hybrid_workspace_bytes(const pl_geometry* g, const pl_image_grid* grid, cons
     clear_error();
     if (!bytes) return fail(PL_EINVAL, "hybrid_workspace_bytes: null output");
     HybridPlan p;
-    const int rc = make_plan(g, grid, opts, &p);
+    const int rc = cached_plan(g, grid, opts, &p);
     if (rc) return rc;
     *bytes = p.total;
     return PL_OK;

@@ -70,31 +70,6 @@ int plan_axis_fft(int n, AxisFft* out);
 // Writes the tables of f at `tables` (256-byte aligned, f.bytes long).
 int launch_axis_fft_tables(const AxisFft& f, char* tables, hipStream_t s);
 
-}  // namespace pl
-
-struct pl_geometry {
-    int mode = PL_MONO;
-    int n_chords = 0, n_elem = 0, n_tx = 0, n_scan = 0, n_freq = 0, n_ch = 0;
-    double radius = 0, arc_center = 0, spacing = 0, scan_step = 0, scan_z0 = 0;
-    double f_start = 0, f_stop = 0;
-    std::vector<double> tx_off;          // chord-local Tx offsets (multi)
-    std::vector<double> tx, rx;          // [n_ch][2]
-    std::vector<double> z, f, k;         // scan heights, frequencies, wavenumbers
-    std::vector<double> ends;            // [n_chords][2][2]
-    std::vector<double> chan;            // [n_ch][4]: x_T, y_T, x_R, y_R (source of the device copy)
-    mutable std::mutex mu;
-    mutable std::map<int, pl::DeviceTables> dev;
-
-    // Device tables for the current device.  If there are none yet and
-    // upload is true they are allocated and copied in stream order on
-    // `stream` (the copies read chan and k, which live as long as the
-    // handle); with upload false that is an error (PL_EINVAL).
-    int device_tables(pl::DeviceTables* out, hipStream_t stream = nullptr, bool upload = true) const;
-    ~pl_geometry();
-};
-
-namespace pl {
-
 // Host-side plan of a hybrid reconstruction: every size and scalar the
 // kernels need, and the workspace layout.
 struct HybridPlan {
@@ -132,6 +107,44 @@ struct HybridPlan {
     size_t off_deap = 0, off_kp = 0, off_wk = 0, off_krz = 0, off_mfma_a = 0, off_mfma_b = 0, off_tiles = 0,
            off_qexp = 0, off_part = 0, total = 0;
 };
+
+}  // namespace pl
+
+struct pl_geometry {
+    int mode = PL_MONO;
+    int n_chords = 0, n_elem = 0, n_tx = 0, n_scan = 0, n_freq = 0, n_ch = 0;
+    double radius = 0, arc_center = 0, spacing = 0, scan_step = 0, scan_z0 = 0;
+    double f_start = 0, f_stop = 0;
+    std::vector<double> tx_off;          // chord-local Tx offsets (multi)
+    std::vector<double> tx, rx;          // [n_ch][2]
+    std::vector<double> z, f, k;         // scan heights, frequencies, wavenumbers
+    std::vector<double> ends;            // [n_chords][2][2]
+    std::vector<double> chan;            // [n_ch][4]: x_T, y_T, x_R, y_R (source of the device copy)
+    mutable std::mutex mu;
+    mutable std::map<int, pl::DeviceTables> dev;
+    // Plans of the last grids and options asked for, by value (the geometry
+    // never changes): a call that repeats one takes a copy of about 3 KB
+    // instead of planning again, twice per call with the workspace query.
+    // At most kPlanCache entries, replaced in turn, freed with the handle.
+    struct CachedPlan {
+        pl_image_grid grid;
+        pl_hybrid_opts opts;
+        pl::HybridPlan plan;
+    };
+    static constexpr size_t kPlanCache = 8;
+    mutable std::mutex plan_mu;
+    mutable std::vector<CachedPlan> plans;
+    mutable size_t next_plan = 0;
+
+    // Device tables for the current device.  If there are none yet and
+    // upload is true they are allocated and copied in stream order on
+    // `stream` (the copies read chan and k, which live as long as the
+    // handle); with upload false that is an error (PL_EINVAL).
+    int device_tables(pl::DeviceTables* out, hipStream_t stream = nullptr, bool upload = true) const;
+    ~pl_geometry();
+};
+
+namespace pl {
 
 // Per (pixel tile, channel) geometry, computed once per call in float64
 // (tile-major: entry tile * n_ch + c).  A pixel's range follows from the
@@ -173,6 +186,8 @@ int launch_gather_batch(const void* descs, const void* items, const int* bounds,
                         int kb, int rsc, size_t smem, int blocks, hipStream_t s);
 int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,
               HybridPlan* p);
+// make_plan through the geometry's cache of plans.
+int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* p);
 
 // The hybrid reconstruction (reconstruct_hybrid and its variants): tables =
 // false skips the plan-table step (ws prepared by hybrid_prepare); upload =

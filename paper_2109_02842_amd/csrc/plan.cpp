@@ -437,4 +437,30 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
     return PL_OK;
 }
 
+// The key is compared byte by byte, so it must hold no padding.
+static_assert(sizeof(pl_image_grid) == 2 * sizeof(int32_t) + 4 * sizeof(double), "padding in pl_image_grid");
+static_assert(sizeof(pl_hybrid_opts) == 10 * sizeof(int32_t) + 2 * sizeof(double), "padding in pl_hybrid_opts");
+
+int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* out) {
+    if (!g || !grid || !out) return make_plan(g, grid, opts, out);   // its error
+    const pl_hybrid_opts key = opts ? *opts : pl_hybrid_opts{};     // no options: all zero
+    {
+        std::lock_guard<std::mutex> lock(g->plan_mu);
+        for (const auto& c : g->plans)
+            if (!std::memcmp(&c.grid, grid, sizeof(*grid)) && !std::memcmp(&c.opts, &key, sizeof(key))) {
+                *out = c.plan;
+                return PL_OK;
+            }
+    }
+    if (int rc = make_plan(g, grid, opts, out)) return rc;   // outside the lock; errors are not kept
+    std::lock_guard<std::mutex> lock(g->plan_mu);
+    if (g->plans.size() < pl_geometry::kPlanCache) {
+        g->plans.push_back({*grid, key, *out});
+    } else {
+        g->plans[g->next_plan] = {*grid, key, *out};
+        g->next_plan = (g->next_plan + 1) % pl_geometry::kPlanCache;
+    }
+    return PL_OK;
+}
+
 }  // namespace pl

@@ -47,7 +47,7 @@ extern "C" int reconstruct_hybrid_static(const pl_geometry* g, const pl_image_gr
     clear_error();
     if (!g || !grid || !echo || !image) return fail(PL_EINVAL, "reconstruct_hybrid_static: null argument");
     HybridPlan p;
-    int rc = make_plan(g, grid, opts, &p);
+    int rc = cached_plan(g, grid, opts, &p);
     if (rc) return rc;
     if (p.total > static_cast<size_t>(PL_STATIC_SCRATCH_BYTES))
         return fail(PL_EWORKSPACE,
