@@ -327,8 +327,11 @@ typedef struct pl_hybrid_plan_info {
 /*
  * Plan sizes for a hybrid reconstruction (host-only).  k_ref_host, if not
  * NULL, receives n_blocks reference wavenumbers (rad/m, for the range
- * rho_T + rho_R; monostatic ranges are 2 rho).  Errors: PL_EINVAL,
- * PL_EUNSUPPORTED (grid or problem beyond the supported sizes).
+ * rho_T + rho_R; monostatic ranges are 2 rho).  The plan is the one of the
+ * steps and the adjoint; a whole FP32 reconstruction that asks for no kernel
+ * may take the matrix-core window form instead (see reconstruct_hybrid), and
+ * workspace_bytes is enough for both.  Errors: PL_EINVAL, PL_EUNSUPPORTED
+ * (grid or problem beyond the supported sizes).
  */
 int hybrid_plan_info(const pl_geometry* geom, const pl_image_grid* grid,
                      const pl_hybrid_opts* opts, pl_hybrid_plan_info* info,
@@ -352,7 +355,12 @@ int hybrid_workspace_bytes(const pl_geometry* geom, const pl_image_grid* grid,
  * The result approximates the exact double sum
  *   G(k_z, p) = sum_c sum_f k_f S[c,k_z,f] exp(j k_rho(f,k_z) l_c(p)),
  *   g = IFFT_kz G,
- * to the tolerance the options set.
+ * to the tolerance the options set.  FP32 plans with the default range method,
+ * interpolation and references, and without a requested tile, block, kernel
+ * or wavefront count, run steps 2 and 3 on a coarser range grid of FP16 pairs
+ * (22 bits) and on the matrix cores with FP32 accumulation, wherever the
+ * planner finds that at a smaller interpolation error than the B-spline's;
+ * mfma_backprojection = -1 asks for the vector kernels.
  *   echo_dev   [n_channels][n_scan][n_freq] complex64, read only.
  *   image_dev  [n_scan][ny][nx] complex64 output; must not alias echo or ws.
  *   ws         device workspace of at least hybrid_workspace_bytes bytes,
@@ -416,8 +424,9 @@ int reconstruct_hybrid_events(const pl_geometry* geom, const pl_image_grid* grid
 /*
  * Adjoint of the imaging operator: image_dev ([z][y][x] complex64) ->
  * echo_dev ([c][m][f] complex64), the conjugate transpose of the linear map
- * echo -> image that reconstruct_hybrid evaluates: the forward transform
- * over z with 1/n_z, the scatter form of the back-projection (eq. 8b/19b
+ * echo -> image that reconstruct_hybrid evaluates with
+ * mfma_backprojection = -1 (the matrix-core form differs from it by its own
+ * and the B-spline's interpolation errors): the forward transform over z with 1/n_z, the scatter form of the back-projection (eq. 8b/19b
  * transposed: each pixel's interpolation taps times the conjugate carrier),
  * the range compression transposed (eq. 8a/19a: for fine grids of 64 R
  * points, R 2,3,5-smooth and at most 32, the exact transpose of the NUFFT
@@ -483,8 +492,9 @@ int kz_ifft(const pl_geometry* geom, const pl_image_grid* grid, const float* spe
  * kernel (PL_BP_PIXEL_LANES, with the k_z block size of the first such scan)
  * runs in one persistent launch per LDS row length (at most 8) that takes
  * (scan, k_z block, pixel tile) work items from device-side queues, one per
- * XCD with stealing, heaviest scans first; other scans' back-projections
- * follow as their own launches.
+ * XCD with stealing, heaviest scans first; scans of the matrix-core window
+ * form share such launches too, one per kernel variant (at most 8), and other
+ * scans' back-projections follow as their own launches.
  *
  * make_hybrid_batch plans the n scans (opts: an array of n, or NULL for the
  * defaults), and uploads the work queue to the current device (a small

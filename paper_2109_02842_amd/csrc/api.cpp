@@ -12,10 +12,11 @@ bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) 
 
 // stage: the single-stage entry points exchange complex64 range profiles,
 // which only the VALU back-projection reads; they plan without the
-// matrix-core back-projection.
+// matrix-core back-projection.  whole: a whole reconstruction, which may take
+// the window back-projection (make_call_plan).
 int prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, void* ws, size_t ws_bytes,
             HybridPlan* p, DeviceTables* dt, const char* what, hipStream_t stream, bool stage = false,
-            bool upload = true) {
+            bool upload = true, bool whole = false) {
     pl_hybrid_opts o{};
     if (opts) o = *opts;
     if (stage) {
@@ -23,12 +24,12 @@ int prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opt
             return fail(PL_EUNSUPPORTED, "%s: the MFMA back-projection runs only inside reconstruct_hybrid", what);
         o.mfma_backprojection = -1;
     }
-    int rc = cached_plan(g, grid, (opts || stage) ? &o : nullptr, p);
+    int rc = cached_plan(g, grid, whole ? opts : &o, whole, p);
     if (rc) return rc;
     if (!ws) return fail(PL_EWORKSPACE, "%s: null workspace", what);
     if (!aligned256(ws)) return fail(PL_EWORKSPACE, "%s: workspace must be 256-byte aligned", what);
-    if (ws_bytes < p->total)
-        return fail(PL_EWORKSPACE, "%s: workspace of %zu bytes, %zu needed", what, ws_bytes, p->total);
+    if (ws_bytes < p->need)
+        return fail(PL_EWORKSPACE, "%s: workspace of %zu bytes, %zu needed", what, ws_bytes, p->need);
     return g->device_tables(dt, stream, upload);
 }
 
@@ -54,7 +55,7 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     clear_error();
     if (!info) return fail(PL_EINVAL, "hybrid_plan_info: null info");
     HybridPlan p;
-    const int rc = cached_plan(g, grid, opts, &p);
+    const int rc = cached_plan(g, grid, opts, false, &p);
     if (rc) return rc;
     info->n_kz = p.n_z;
     info->n_l = p.n_l;
@@ -70,7 +71,9 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     info->waves = p.waves;
     info->du = p.du;
     info->beta = p.beta;
-    info->workspace_bytes = p.total;
+    HybridPlan call;
+    if (const int rc2 = cached_plan(g, grid, opts, true, &call)) return rc2;
+    info->workspace_bytes = call.need;
     info->range_method = p.range_method;
     info->dk_uniform = p.range_method == PL_RANGE_RESAMPLE ? p.dkl : 0.0;
     info->scan_fft_len = p.zfft.m;
@@ -85,9 +88,9 @@ int hybrid_workspace_bytes(const pl_geometry* g, const pl_image_grid* grid, cons
     clear_error();
     if (!bytes) return fail(PL_EINVAL, "hybrid_workspace_bytes: null output");
     HybridPlan p;
-    const int rc = cached_plan(g, grid, opts, &p);
+    const int rc = cached_plan(g, grid, opts, true, &p);
     if (rc) return rc;
-    *bytes = p.total;
+    *bytes = p.need;
     return PL_OK;
 }
 
@@ -193,7 +196,7 @@ int reconstruct_impl(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     if (!echo || !image) return fail(PL_EINVAL, "%s: null echo or image", what);
     HybridPlan p;
     DeviceTables dt;
-    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, what, stream, false, upload);
+    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, what, stream, false, upload, true);
     if (rc) return rc;
     auto mark = [&](int i) -> int {
         if (ev && ev[i] && hipEventRecord(ev[i], stream) != hipSuccess)
@@ -209,7 +212,12 @@ int reconstruct_impl(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     if ((rc = mark(1)) || (rc = launch_scan_fft(g, reinterpret_cast<const float2*>(echo), spec, p.zfft, ztab, stream)))
         return rc;
     if ((rc = mark(2))) return rc;
-    if (p.bp_mfma) {
+    if (p.bp_window) {
+        unsigned* qw = reinterpret_cast<unsigned*>(w + p.off_q);   // hi + lo FP16 planes, the bytes of complex64
+        if ((rc = launch_spectrum_max(p, spec, w, stream))) return rc;
+        if ((rc = launch_range_compress_window(p, spec, w, qw, stream))) return rc;
+        if ((rc = mark(3)) || (rc = launch_backproject_window(p, qw, w, G, stream))) return rc;
+    } else if (p.bp_mfma) {
         // split BF16 profiles in the same bytes as the complex64 ones
         unsigned short* qs = reinterpret_cast<unsigned short*>(w + p.off_q);
         if ((rc = launch_range_compress_mfma_split(p, spec, w, qs, stream))) return rc;
@@ -247,7 +255,7 @@ int hybrid_prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hyb
     clear_error();
     HybridPlan p;
     DeviceTables dt;
-    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, "hybrid_prepare", stream);
+    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, "hybrid_prepare", stream, false, true, true);
     if (rc) return rc;
     return launch_plan_tables(p, dt, static_cast<char*>(ws), stream);
 }

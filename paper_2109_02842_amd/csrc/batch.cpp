@@ -19,6 +19,8 @@ struct pl_hybrid_batch {
     // One persistent launch: the queued scans of one LDS row length.
     struct Queue {
         int kb = 0, rsc = 0, n_items = 0, grid = 0;
+        int wch = 0, step = 0;  // window back-projection: chunks per row (0: pixel per lane), start step
+        bool mono = false;
         size_t smem = 0, items_off = 0, bounds_off = 0;  // byte offsets in d_items
     };
     int device = -1;
@@ -29,9 +31,11 @@ struct pl_hybrid_batch {
     std::vector<char> in_queue;         // scan takes part in a persistent launch
     std::vector<Queue> queues;
     void* d_desc = nullptr;             // device: per-scan descriptors
+    void* d_win = nullptr;              // device: per-scan descriptors of the window back-projection
     void* d_items = nullptr;            // device: per queue, int4 work items then 9 bounds
     ~pl_hybrid_batch() {
         if (d_desc) (void)hipFree(d_desc);
+        if (d_win) (void)hipFree(d_win);
         if (d_items) (void)hipFree(d_items);
     }
 };
@@ -65,13 +69,13 @@ int make_hybrid_batch(int32_t n, const pl_geometry* const* geoms, const pl_image
     size_t off = 0;
     for (int s = 0; s < n; ++s) {
         if (!geoms[s]) return bail(fail(PL_EINVAL, "make_hybrid_batch: scan %d has no geometry", s));
-        int rc = cached_plan(geoms[s], &grids[s], opts ? &opts[s] : nullptr, &b->plans[s]);
+        int rc = cached_plan(geoms[s], &grids[s], opts ? &opts[s] : nullptr, true, &b->plans[s]);
         if (rc) return bail(rc);
         b->ws_off[s] = off;
         off = align256(off + b->plans[s].total);
     }
-    b->counter_off = off;  // eight counters per persistent launch (at most 8 launches)
-    b->total = off + 256;
+    b->counter_off = off;  // eight counters per persistent launch (at most 16 launches)
+    b->total = off + 512;
 
     // Scans in the persistent launches: pixel-per-lane plans sharing the k_z
     // block size of the first such scan, one launch per LDS row length (a
@@ -88,8 +92,64 @@ int make_hybrid_batch(int32_t n, const pl_geometry* const* geoms, const pl_image
     }
     if (rscs.size() > 8) return bail(fail(PL_EUNSUPPORTED, "make_hybrid_batch: more than 8 row lengths"));
     std::sort(rscs.begin(), rscs.end());
-    std::vector<char> desc(gather_batch_desc_bytes() * n, 0);
+    std::vector<char> desc(gather_batch_desc_bytes() * n, 0), win(window_batch_desc_bytes() * n, 0);
     std::vector<int> all;  // every queue's items and bounds, back to back
+    // eight per-XCD item lists to a queue
+    auto add_queue = [&](pl_hybrid_batch::Queue q, const std::vector<std::vector<int>>& per_xcd) {
+        std::vector<int> items;
+        std::vector<int> bounds(9, 0);
+        for (int x = 0; x < 8; ++x) {
+            items.insert(items.end(), per_xcd[x].begin(), per_xcd[x].end());
+            bounds[x + 1] = static_cast<int>(items.size() / 4);
+        }
+        q.n_items = static_cast<int>(items.size() / 4);
+        q.items_off = all.size() * sizeof(int);
+        all.insert(all.end(), items.begin(), items.end());
+        q.bounds_off = all.size() * sizeof(int);
+        all.insert(all.end(), bounds.begin(), bounds.end());
+        while (all.size() % 4) all.push_back(0);  // keep the next queue's items 16-byte aligned
+        b->queues.push_back(q);
+    };
+    // The window back-projection's scans: one queue per kernel variant, the
+    // same items (and split pieces) as the scans' single calls, in the same
+    // per-XCD order as below.
+    for (int wch = 8; wch <= 9; ++wch)
+        for (int step = 1; step <= 2; ++step)
+            for (int mono = 0; mono < 2; ++mono) {
+                std::vector<int> order;
+                for (int s = 0; s < n; ++s) {
+                    const HybridPlan& p = b->plans[s];
+                    if (p.bp_window && p.window == 4 * wch && p.win_step == step && (p.mode == PL_MONO) == (mono != 0))
+                        order.push_back(s);
+                }
+                if (order.empty()) continue;
+                std::stable_sort(order.begin(), order.end(),
+                                 [&](int i, int j) { return b->plans[i].n_ch > b->plans[j].n_ch; });
+                pl_hybrid_batch::Queue q;
+                q.wch = wch;
+                q.step = step;
+                q.mono = mono != 0;
+                std::vector<std::vector<int>> per_xcd(8);
+                for (int s : order) {
+                    b->in_queue[s] = 1;
+                    DeviceTables dt;
+                    int n_whole = 0, n_pieces = 0, rc = geoms[s]->device_tables(&dt);
+                    if (rc) return bail(rc);
+                    if ((rc = build_window_batch_desc(b->plans[s], b->ws_off[s], win.data() + window_batch_desc_bytes() * s,
+                                                      &n_whole, &n_pieces)))
+                        return bail(rc);
+                    for (int k = 0; k < 2; ++k) {
+                        const int m = k ? n_pieces : n_whole;
+                        for (int i = 0; i < m; ++i) {
+                            auto& list = per_xcd[static_cast<size_t>((static_cast<long long>(i) * 8) / m)];
+                            for (int v : {s, k ? -1 : i, k ? i : 0, 0}) list.push_back(v);
+                        }
+                    }
+                }
+                int rc = window_batch_grid(wch, step, mono != 0, &q.grid);
+                if (rc) return bail(rc);
+                add_queue(q, per_xcd);
+            }
     for (int rsc : rscs) {
         pl_hybrid_batch::Queue q;
         q.kb = kb;
@@ -127,24 +187,13 @@ int make_hybrid_batch(int32_t n, const pl_geometry* const* geoms, const pl_image
                 per_xcd[x].push_back(0);
             }
         }
-        std::vector<int> items;
-        std::vector<int> bounds(9, 0);
-        for (int x = 0; x < 8; ++x) {
-            items.insert(items.end(), per_xcd[x].begin(), per_xcd[x].end());
-            bounds[x + 1] = static_cast<int>(items.size() / 4);
-        }
-        q.n_items = static_cast<int>(items.size() / 4);
-        q.items_off = all.size() * sizeof(int);
-        all.insert(all.end(), items.begin(), items.end());
-        q.bounds_off = all.size() * sizeof(int);
-        all.insert(all.end(), bounds.begin(), bounds.end());
-        while (all.size() % 4) all.push_back(0);  // keep the next queue's items 16-byte aligned
         int rc = gather_batch_grid(kb, rsc, q.smem, &q.grid);
         if (rc) return bail(rc);
-        b->queues.push_back(q);
+        add_queue(q, per_xcd);
     }
     if (!b->queues.empty() &&
-        (hipMalloc(&b->d_desc, desc.size()) != hipSuccess || hipMalloc(&b->d_items, all.size() * sizeof(int)) != hipSuccess ||
+        (hipMalloc(&b->d_desc, desc.size()) != hipSuccess || hipMalloc(&b->d_win, win.size()) != hipSuccess ||
+         hipMemcpy(b->d_win, win.data(), win.size(), hipMemcpyHostToDevice) != hipSuccess || hipMalloc(&b->d_items, all.size() * sizeof(int)) != hipSuccess ||
          hipMemcpy(b->d_desc, desc.data(), desc.size(), hipMemcpyHostToDevice) != hipSuccess ||
          hipMemcpy(b->d_items, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess))
         return bail(fail(PL_EDEVICE, "make_hybrid_batch: uploading the work queues failed"));
@@ -222,7 +271,10 @@ int batch_impl(const pl_hybrid_batch* b, const float* const* echoes, float* cons
         if ((rc = launch_scan_fft(b->geoms[s], reinterpret_cast<const float2*>(echoes[s]), spec, p.zfft,
                                   ws_s + p.off_zfft, stream)))
             return rc;
-        if (p.bp_mfma)
+        if (p.bp_window) {
+            if (!(rc = launch_spectrum_max(p, spec, ws_s, stream)))
+                rc = launch_range_compress_window(p, spec, ws_s, reinterpret_cast<unsigned*>(ws_s + p.off_q), stream);
+        } else if (p.bp_mfma)
             rc = launch_range_compress_mfma_split(p, spec, ws_s, reinterpret_cast<unsigned short*>(ws_s + p.off_q), stream);
         else if (p.precision == PL_PREC_FP32)
             rc = launch_range_compress_fp32(p, spec, ws_s, reinterpret_cast<float2*>(ws_s + p.off_q), stream);
@@ -234,14 +286,22 @@ int batch_impl(const pl_hybrid_batch* b, const float* const* echoes, float* cons
     for (size_t k = 0; k < b->queues.size(); ++k) {
         const auto& q = b->queues[k];
         const char* base = static_cast<const char*>(b->d_items);
+        if (q.wch) {
+            if ((rc = launch_window_batch(b->d_win, base + q.items_off, reinterpret_cast<const int*>(base + q.bounds_off),
+                                          reinterpret_cast<unsigned*>(w + b->counter_off) + 8 * k, w, q.wch, q.step, q.mono,
+                                          q.grid, stream)))
+                return rc;
+            continue;
+        }
         if ((rc = launch_gather_batch(b->d_desc, base + q.items_off, reinterpret_cast<const int*>(base + q.bounds_off),
                                       reinterpret_cast<unsigned*>(w + b->counter_off) + 8 * k, w, q.kb, q.rsc, q.smem,
                                       q.grid, stream)))
             return rc;
     }
     for (int s = 0; s < n; ++s) {
-        if (b->in_queue[s]) continue;
         const HybridPlan& p = b->plans[s];
+        if (p.bp_window && (rc = launch_window_combine(p, w + b->ws_off[s], stream))) return rc;
+        if (b->in_queue[s]) continue;
         char* ws_s = w + b->ws_off[s];
         float2* G = reinterpret_cast<float2*>(ws_s + p.off_G);
         rc = p.bp_mfma ? launch_backproject_mfma(p, dts[s], reinterpret_cast<const unsigned short*>(ws_s + p.off_q),

@@ -29,6 +29,13 @@ constexpr size_t kMaxLds = 160 * 1024;          // LDS per workgroup on gfx950
 constexpr int kMaxFreq = 1024;
 constexpr int kMaxFine = 4096;      // NUFFT fine grid held twice in LDS (64 KiB)
 constexpr double kNufftUpsample = 1.25;  // FP32 NUFFT: fine grid of at least 1.25 n_l points
+// window back-projection: k_z bins per block beside their mirrors, and
+// coefficients of the even and odd parts of its weight polynomials
+constexpr int kWindowBins = 32;
+constexpr int kWindowDegree = 5;
+constexpr int kSpectrumMaxParts = 256;
+constexpr int kMaxWindowPieces = 512;      // partial spectra of split items (16x16 pixels x 64 rows)
+constexpr size_t kWindowPieceBytes = 16ull * 16 * 2 * kWindowBins * 8;
 constexpr int kMaxGL = 64;          // quadrature nodes for the kernel transform
 constexpr int kMaxRadices = 16;
 
@@ -83,6 +90,17 @@ struct HybridPlan {
     int force_tile = 0, force_tile_y = 0, force_kpl = 0, force_waves = 0, force_bp_mfma = 0, force_kb = 0;
     bool bp_mfma = false;            // back-projection on the matrix cores (split-BF16 q)
     bool bp_mfma_sp = false;         // its single-pass form (scaled FP16 q, one product per pair)
+    // whole FP32 calls: back-projection on the matrix cores from hi + lo FP16
+    // profiles, eight range samples per 4x4 pixel group (plan: window_plan);
+    // its blocks are kWindowBins k_z bins and their mirrors n_z - 1 - kz
+    bool bp_window = false;
+    double win_span = 0;             // samples a group's ranges may span
+    int win_step = 2;                // its window starts are multiples of this many samples
+    double win_z = 0;                // weight polynomials in z = win_z x^2 - 1
+    float win_even[kWindowDegree][4] = {}, win_odd[kWindowDegree][4] = {};
+    int log2_gain = 0, part_pieces = 0;
+    double span = 0;                 // widest range interval of a channel over the image
+    double lo_margin = 2;            // range samples before a channel's lowest range
     bool bp_gather = false;          // VALU back-projection with one pixel per lane
     int range_method = PL_RANGE_NUFFT;
     int ref_mode = PL_REF_BAND_CENTRE;  // reference wavenumber: per k_z block, or the paper's per k_z
@@ -105,7 +123,8 @@ struct HybridPlan {
     // workspace layout (byte offsets, 256-aligned)
     size_t off_spec = 0, off_q = 0, off_G = 0, off_llo = 0, off_lref = 0, off_zfft = 0, off_tw_fine = 0;
     size_t off_deap = 0, off_kp = 0, off_wk = 0, off_krz = 0, off_mfma_a = 0, off_mfma_b = 0, off_tiles = 0,
-           off_qexp = 0, off_part = 0, total = 0;
+           off_qexp = 0, off_part = 0, off_smax = 0, total = 0;
+    size_t need = 0;  // bytes a caller's workspace must hold: the larger of the call's plans
 };
 
 }  // namespace pl
@@ -123,12 +142,13 @@ struct pl_geometry {
     mutable std::mutex mu;
     mutable std::map<int, pl::DeviceTables> dev;
     // Plans of the last grids and options asked for, by value (the geometry
-    // never changes): a call that repeats one takes a copy of about 3 KB
+    // never changes): a call that repeats one takes a copy of about 4 KB
     // instead of planning again, twice per call with the workspace query.
     // At most kPlanCache entries, replaced in turn, freed with the handle.
     struct CachedPlan {
         pl_image_grid grid;
         pl_hybrid_opts opts;
+        bool whole;   // make_call_plan's, else make_plan's
         pl::HybridPlan plan;
     };
     static constexpr size_t kPlanCache = 8;
@@ -186,8 +206,13 @@ int launch_gather_batch(const void* descs, const void* items, const int* bounds,
                         int kb, int rsc, size_t smem, int blocks, hipStream_t s);
 int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,
               HybridPlan* p);
-// make_plan through the geometry's cache of plans.
-int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* p);
+// The plan of a whole reconstruction: the window back-projection's where the
+// options leave the kernel open and its error estimate allows it, else
+// make_plan's (which the stage calls, the adjoint and hybrid_plan_info use).
+int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* p);
+// make_plan, or with whole make_call_plan, through the geometry's cache of plans.
+int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, bool whole, HybridPlan* p);
+size_t backproject_window_lds_bytes(int chunks);
 
 // The hybrid reconstruction (reconstruct_hybrid and its variants): tables =
 // false skips the plan-table step (ws prepared by hybrid_prepare); upload =
@@ -220,6 +245,20 @@ int launch_backproject(const HybridPlan& p, const DeviceTables& dt, const float2
                        float2* G, hipStream_t s);
 int launch_backproject_mfma(const HybridPlan& p, const DeviceTables& dt, const unsigned short* qs,
                             char* ws, float2* G, hipStream_t s);
+// Window plans: parts of the spectrum's largest value (the profiles' scale),
+// the range compression into hi + lo FP16 planes, the back-projection.
+int launch_spectrum_max(const HybridPlan& p, const float2* spec, char* ws, hipStream_t s);
+int launch_range_compress_window(const HybridPlan& p, const float2* spec, char* ws, unsigned* q, hipStream_t s);
+int launch_backproject_window(const HybridPlan& p, const unsigned* q, char* ws, float2* G, hipStream_t s);
+// Its batched form, as the pixel-per-lane kernel's above: items are int4
+// (scan, work item, 0, 0), or (scan, -1, piece, 0) for the pieces of a
+// scan's split items, which launch_window_combine adds up afterwards.
+size_t window_batch_desc_bytes();
+int build_window_batch_desc(const HybridPlan& p, size_t ws_off, void* out, int* n_whole, int* n_pieces);
+int window_batch_grid(int wch, int step, bool mono, int* blocks);
+int launch_window_batch(const void* descs, const void* items, const int* bounds, unsigned* counters, char* ws, int wch,
+                        int step, bool mono, int blocks, hipStream_t s);
+int launch_window_combine(const HybridPlan& p, char* ws, hipStream_t s);
 int launch_kz_ifft(const HybridPlan& p, const float2* G, float2* image, const char* tables, hipStream_t s);
 // Adjoint steps (image -> echo), in the order they run.
 int launch_kz_fft_adjoint(const HybridPlan& p, const float2* image, float2* Gt, const char* tables, hipStream_t s);

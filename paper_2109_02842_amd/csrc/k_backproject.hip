@@ -488,14 +488,15 @@ __global__ __launch_bounds__(64 * kGatherWaves) void backproject_gather_kernel(c
 }
 
 struct TileTableArgs {
-    int n_ch, n_l, tiles_x, n_tiles, tile_x, tile_y, wpl, n_blocks;
+    int n_ch, n_l, tiles_x, n_tiles, tile_x, tile_y, wpl, n_blocks, align, first;
+    double shift;   // window start: this many samples from the tile's lowest range
     double x0, y0, dx, dy, inv_du, reach;
     double kref[kMaxBlocks];
 };
 
 // The tile table (see GatherTileEntry), one thread per (tile, channel): the
 // tile's centre, its range from the channel's antennas in float64, the
-// even start of the channel's staged window (wpl samples) and the centre's
+// aligned start of the channel's staged window (wpl samples) and the centre's
 // first tap and fractional position relative to it; then the centre's
 // carrier for every k_z block (after the entries).
 __global__ void tile_table_kernel(TileTableArgs a, const double* __restrict__ chan, const double* __restrict__ llo,
@@ -511,8 +512,8 @@ __global__ void tile_table_kernel(TileTableArgs a, const double* __restrict__ ch
         const double xt = cx - ch[0], yt = cy - ch[1], xr = cx - ch[2], yr = cy - ch[3];
         const double dt = sqrt(xt * xt + yt * yt), dr = sqrt(xr * xr + yr * yr);
         const double l = dt + dr;
-        int s = static_cast<int>(floor((l - a.reach - llo[c]) * a.inv_du)) - 2;
-        s = max(0, min(s, a.n_l - a.wpl)) & ~1;
+        int s = static_cast<int>(floor((l - a.reach - llo[c]) * a.inv_du + a.shift));
+        s = max(a.first, min(s, a.n_l - a.wpl)) & ~(a.align - 1);
         const double u = (l - llo[c]) * a.inv_du;
         const double fl = floor(u);
         GatherTileEntry t;
@@ -723,13 +724,13 @@ size_t backproject_gather_lds_bytes(int rows, int row_chunks) {
 }
 
 size_t tile_table_bytes(const HybridPlan& p) {
-    return (p.bp_gather || p.bp_mfma)
+    return (p.bp_gather || p.bp_mfma || p.bp_window)
                ? static_cast<size_t>(p.tiles_x) * p.tiles_y * p.n_ch * (sizeof(GatherTileEntry) + p.n_blocks * sizeof(float2))
                : 0;
 }
 
 int launch_tile_tables(const HybridPlan& p, const DeviceTables& dt, char* ws, hipStream_t s) {
-    if (!p.bp_gather && !p.bp_mfma) return PL_OK;
+    if (!p.bp_gather && !p.bp_mfma && !p.bp_window) return PL_OK;
     TileTableArgs a{};
     a.n_ch = p.n_ch;
     a.n_l = p.n_l;
@@ -737,7 +738,12 @@ int launch_tile_tables(const HybridPlan& p, const DeviceTables& dt, char* ws, hi
     a.n_tiles = p.tiles_x * p.tiles_y;
     a.tile_x = p.tile_x;
     a.tile_y = p.tile_y;
-    a.wpl = p.bp_gather ? p.window : 8 * (p.window / 8);  // staged samples per row (plane)
+    a.wpl = p.bp_mfma ? 8 * (p.window / 8) : p.window;  // staged samples per row (plane)
+    a.align = p.bp_window ? 4 : 2;
+    a.first = p.bp_window ? 4 : 0;   // rows may be staged from two samples earlier
+    // a window group's samples start up to 3.5 samples and half a step, less
+    // half its span, before its lowest pixel; the other kernels' first tap is one before
+    a.shift = p.bp_window ? 0.5 * (p.win_span - p.win_step) - 4.1 : -2.0;
     a.x0 = p.x0;
     a.y0 = p.y0;
     a.dx = p.dx;

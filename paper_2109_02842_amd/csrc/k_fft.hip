@@ -6,7 +6,8 @@ namespace pl {
 namespace {
 
 struct PlanTablesArgs {
-    int n_ch, n_z, n_f, n_l, n_fine, interp, n_gl, block, ref_mode;
+    int n_ch, n_z, n_f, n_l, n_fine, interp, n_gl, block, ref_mode, mirror;
+    double lo_margin;
     double du, h, beta, scan_step;
     double gx0, gx1, gy0, gy1;
     double kref[kMaxBlocks];
@@ -21,6 +22,7 @@ __device__ double kz_of(int kap, int n_z, double step) {
 
 // Reference wavenumber of k_z bin kap (see plan_tables_kernel).
 __device__ double kref_of(const PlanTablesArgs& a, const double* __restrict__ k, int kap) {
+    if (a.mirror) return a.kref[min(kap, a.n_z - 1 - kap) / a.block];   // blocks of bins and their mirrors
     if (a.ref_mode != PL_REF_MIN_K) return a.kref[kap / a.block];
     const double q = 0.25 * kz_of(kap, a.n_z, a.scan_step) * kz_of(kap, a.n_z, a.scan_step);
     for (int f = 0; f < a.n_f; ++f) {   // k rises with f: the first real k_rho is the smallest
@@ -37,7 +39,7 @@ __device__ double dist_to_rect(double px, double py, double x0, double x1, doubl
 
 // Fills the per-call tables of the hybrid plan:
 //   llo[c]       start of channel c's range grid (lowest range over the pixel
-//                rectangle minus two steps)
+//                rectangle minus lo_margin steps)
 //   lref[c]      range rho_T + rho_R from channel c to the centre of the pixel
 //                rectangle (demodulation reference of the resampling method)
 //   tw_fine[t]   exp(-2 pi i t / n_fine)
@@ -61,7 +63,7 @@ __global__ void plan_tables_kernel(PlanTablesArgs a, const double* __restrict__ 
             const int c = static_cast<int>(idx);
             const double lmin = dist_to_rect(chan[4 * c], chan[4 * c + 1], a.gx0, a.gx1, a.gy0, a.gy1) +
                                 dist_to_rect(chan[4 * c + 2], chan[4 * c + 3], a.gx0, a.gx1, a.gy0, a.gy1);
-            llo[c] = lmin - 2.0 * a.du;
+            llo[c] = lmin - a.lo_margin * a.du;
             const double cx = 0.5 * (a.gx0 + a.gx1), cy = 0.5 * (a.gy0 + a.gy1);
             lref[c] = hypot(cx - chan[4 * c], cy - chan[4 * c + 1]) + hypot(cx - chan[4 * c + 2], cy - chan[4 * c + 3]);
         } else if (idx < n1) {
@@ -671,10 +673,12 @@ int launch_plan_tables(const HybridPlan& p, const DeviceTables& dt, char* ws, hi
     a.n_f = p.n_f;
     a.n_l = p.n_l;
     a.n_fine = p.n_fine;
-    a.interp = p.interp;
+    a.interp = p.bp_window ? PL_INTERP_LAGRANGE4 : p.interp;   // the window weights take no prefilter
     a.n_gl = p.n_gl;
     a.block = p.block;
     a.ref_mode = p.ref_mode;
+    a.mirror = p.bp_window;
+    a.lo_margin = p.lo_margin;
     a.du = p.du;
     a.h = p.h;
     a.beta = p.beta;

@@ -217,8 +217,11 @@ __global__ __launch_bounds__(256) void resample_kernel(const float2* __restrict_
 // at most 32): one wavefront owns one (channel, k_z) pair and its LDS, so
 // the kernel has no workgroup barriers; the inverse FFT is wave_ifft.
 
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
 struct NufftWaveArgs {
-    int n_z, n_f, n_l, n_pairs;
+    int n_z, n_f, n_l, n_pairs, log2_gain;
+    const float* smax;   // HILO: parts of the spectrum's largest value
     double du, h, beta, inv_h;
 };
 
@@ -226,8 +229,11 @@ struct NufftWaveArgs {
 constexpr size_t nufft_wave_lds(int r, int n_f) { return 16ull * n_f + 8ull * r * kWaveRow; }
 
 // One workgroup (one wavefront) per (channel c, k_z bin kap); the same
-// strengths, spreading and deapodisation as nufft_kernel.
-template <int R>
+// strengths, spreading and deapodisation as nufft_kernel.  HILO: the profiles
+// are written scaled by 2^-g (profile_exponent) as FP16 pairs hi + lo, two
+// planes per pair (hi, then lo; one word of (Re, Im) per sample) in the bytes
+// of the complex64 profiles.
+template <int R, bool HILO>
 __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict__ spec,
                                                        const double* __restrict__ llo,
                                                        const double* __restrict__ kp,
@@ -247,6 +253,7 @@ __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict
     const double lmid = llo[c] + (a.n_l / 2) * a.du;
     const double cell = a.du * N * (0.5 / kPi);
 
+    const int g = HILO ? profile_exponent(a.smax, a.log2_gain, lane) : 0;
     // strengths and positions; first propagating frequency by ballot
     int f0 = a.n_f;
     for (int fb = 0; fb < a.n_f; fb += 64) {
@@ -255,6 +262,7 @@ __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict
         if (f < a.n_f) {
             const double kpf = kp[static_cast<size_t>(kap) * a.n_f + f];
             w = wk[static_cast<size_t>(kap) * a.n_f + f];
+            if (HILO) w = ldexpf(w, -g);
             const float2 sv = spec[static_cast<size_t>(pair) * a.n_f + f];
             pa[f] = cscale(cmul(sv, cis(kpf * lmid)), w);
             py[f] = kpf * cell;
@@ -263,7 +271,7 @@ __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict
         if (f0 == a.n_f && m) f0 = fb + __ffsll(static_cast<long long>(m)) - 1;
     }
     float2* qo = q + static_cast<size_t>(pair) * a.n_l;
-    if (f0 >= a.n_f) {  // nothing propagates at this k_z
+    if (f0 >= a.n_f) {  // nothing propagates at this k_z (all bits zero in both forms)
         for (int i = lane; i < a.n_l; i += 64) qo[i] = make_float2(0.f, 0.f);
         return;
     }
@@ -304,11 +312,26 @@ __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict
     wave_ifft<R>(A, tw, lane, [&](int k, float2 v) {
         // deapodised into q[i] for k = (i - n_l / 2) mod N
         const int i = k < half ? k + half : k - N + half;
-        if (i >= 0 && i < a.n_l) qo[i] = cscale(v, dp[i]);
+        if (i < 0 || i >= a.n_l) return;
+        v = cscale(v, dp[i]);
+        if constexpr (HILO) {
+            unsigned* qw = reinterpret_cast<unsigned*>(qo);
+            // the rounded products: left to itself the compiler converts the
+            // product once rounded for hi and unrounded for lo, and near a
+            // tie (one value in 2^13) the two disagree by a unit of hi
+            asm volatile("" : "+v"(v.x), "+v"(v.y));
+            const f16x2 h = {static_cast<_Float16>(v.x), static_cast<_Float16>(v.y)};
+            const f16x2 l = {static_cast<_Float16>(v.x - static_cast<float>(h[0])),
+                             static_cast<_Float16>(v.y - static_cast<float>(h[1]))};
+            qw[i] = __builtin_bit_cast(unsigned, h);
+            qw[a.n_l + i] = __builtin_bit_cast(unsigned, l);
+        } else {
+            qo[i] = v;
+        }
     });
 }
 
-template <int R>
+template <int R, bool HILO>
 int launch_nufft_wave(const HybridPlan& p, const float2* spec, char* ws, float2* q, hipStream_t s) {
     NufftWaveArgs a{};
     a.n_z = p.n_z;
@@ -321,8 +344,10 @@ int launch_nufft_wave(const HybridPlan& p, const float2* spec, char* ws, float2*
     a.h = p.h;
     a.inv_h = 1.0 / p.h;
     a.beta = p.beta;
+    a.smax = reinterpret_cast<const float*>(ws + p.off_smax);
+    a.log2_gain = p.log2_gain;
     const size_t smem = nufft_wave_lds(R, p.n_f);
-    auto fn = nufft_wave_kernel<R>;
+    auto fn = nufft_wave_kernel<R, HILO>;
     if (smem > 65536) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
@@ -463,7 +488,7 @@ int launch_range_compress_fp32(const HybridPlan& p, const float2* spec, char* ws
     a.rad = p.fine_rad;
     if (p.n_fine % 64 == 0) {
 #define PL_NW(R) \
-        if (p.n_fine == 64 * R) return launch_nufft_wave<R>(p, spec, ws, q, s);
+        if (p.n_fine == 64 * R) return launch_nufft_wave<R, false>(p, spec, ws, q, s);
         PL_NUFFT_WAVE_SIZES(PL_NW)
 #undef PL_NW
     }
@@ -476,6 +501,14 @@ int launch_range_compress_fp32(const HybridPlan& p, const float2* spec, char* ws
                        reinterpret_cast<const float*>(ws + p.off_wk), reinterpret_cast<const float2*>(ws + p.off_tw_fine),
                        reinterpret_cast<const float*>(ws + p.off_deap), a, q);
     return check_launch("range compression");
+}
+
+int launch_range_compress_window(const HybridPlan& p, const float2* spec, char* ws, unsigned* q, hipStream_t s) {
+#define PL_NW(R) \
+    if (p.n_fine == 64 * R) return launch_nufft_wave<R, true>(p, spec, ws, reinterpret_cast<float2*>(q), s);
+    PL_NUFFT_WAVE_SIZES(PL_NW)
+#undef PL_NW
+    return fail(PL_EUNSUPPORTED, "hi + lo range profiles need a wavefront fine grid, not %d points", p.n_fine);
 }
 
 }  // namespace pl

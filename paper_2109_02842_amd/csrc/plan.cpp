@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <vector>
 
 #include "internal.hpp"
 
@@ -38,6 +39,317 @@ void gauss_legendre(int n, double* x, double* w) {
 double dist_to_rect(double px, double py, double x0, double x1, double y0, double y1) {
     const double cx = std::min(std::max(px, x0), x1), cy = std::min(std::max(py, y0), y1);
     return std::hypot(px - cx, py - cy);
+}
+
+// Spreading kernel of the NUFFT for the plan's n_l and n_fine; sigma: the
+// range grid's oversampling.
+int set_spreading(HybridPlan* plan, double sigma) {
+    HybridPlan& p = *plan;
+    // Exponential-of-semicircle kernel exp(beta (sqrt(1 - z^2) - 1)) of
+    // width W (Barnett, Magland, af Klinteberg 2019).  For the 2x fine grid:
+    // W = ceil(log10(1/tol)) + 1, beta = 2.30 W.  For an upsampling factor
+    // s = n_fine / n_l below 2, their error estimate exp(-pi W sqrt(1 - 1/s))
+    // gives W = ceil(ln(1/tol) / (pi sqrt(1 - 1/s))), and beta =
+    // 0.97 pi W (1 - 1/(2 s)).
+    const double ups = static_cast<double>(p.n_fine) / p.n_l;
+    if (ups >= 1.999) {
+        p.W = std::max(2, static_cast<int>(std::ceil(std::log10(1.0 / p.tol))) + 1);
+        p.W = std::min(p.W, 16);
+        p.beta = 2.30 * p.W;
+    } else {
+        p.W = std::max(2, static_cast<int>(std::ceil(std::log(1.0 / p.tol) / (kPi * std::sqrt(1.0 - 1.0 / ups)))));
+        p.W = std::min(p.W, 16);
+        p.beta = 0.97 * kPi * p.W * (1.0 - 0.5 / ups);
+    }
+    p.h = 0.5 * p.W;
+    if (p.n_fine / sigma + 2 * p.W + 2 >= p.n_fine) return fail(PL_EUNSUPPORTED, "fine grid too short");
+    p.n_gl = std::min(kMaxGL, 4 * p.W + 16);
+    gauss_legendre(p.n_gl, p.gl_x, p.gl_w);
+    return PL_OK;
+}
+
+// Workspace layout (byte offsets) of the plan.
+int set_layout(HybridPlan* plan) {
+    HybridPlan& p = *plan;
+    const size_t nch = p.n_ch, nz = p.n_z, nf = p.n_f, npix = static_cast<size_t>(p.nx) * p.ny;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off = align256(off + bytes);
+        return o;
+    };
+    p.off_spec = take(nch * nz * nf * 8);
+    p.off_q = take(nch * nz * static_cast<size_t>(p.n_l) * 8);
+    p.off_G = take(npix * nz * 8);
+    p.off_llo = take(nch * 8);
+    p.off_lref = take(nch * 8);
+    p.off_zfft = take(p.zfft.bytes);
+    p.off_tw_fine = take(static_cast<size_t>(p.n_fine) * 8);
+    p.off_deap = take(static_cast<size_t>(p.n_l) * 4);
+    p.off_kp = take(nz * nf * 8);
+    p.off_wk = take(nz * nf * 4);
+    p.off_krz = take(nz * 8);
+    p.off_tiles = take(tile_table_bytes(p));
+    p.off_part = take(p.bp_window ? p.part_pieces * kWindowPieceBytes : backproject_mfma_part_bytes(p));
+    p.off_smax = take(p.bp_window ? kSpectrumMaxParts * sizeof(float) : 0);
+    p.n_chp = (p.n_ch + 31) / 32 * 32;
+    p.n_fp = (p.n_f + 15) / 16 * 16;
+    if (p.precision != PL_PREC_FP32) {
+        if (p.n_fp > 128)
+            return fail(PL_EUNSUPPORTED, "MFMA range compression supports up to 128 frequencies");
+        p.off_mfma_a = take(nz * static_cast<size_t>(p.n_chp) * 4);
+        p.off_qexp = take(4 * (kProfileScaleParts + 1));
+        p.off_mfma_b = take(nz * static_cast<size_t>(p.n_chp) * 4 * p.n_fp * 2);
+    } else {
+        p.off_mfma_a = off;
+        p.off_mfma_b = off;
+        p.off_qexp = off;
+    }
+    p.total = off;
+    return PL_OK;
+}
+
+// Weights of the window back-projection: the least-squares interpolator of
+// e^{j th x} from the eight samples at s - 3.5, for positions |x| <= xm and
+// th spread evenly over each block's band [-X_b, X_b] (X_b = half band x du).
+// Its normal matrix and right-hand side are means of sinc(X_b (s - s')) and
+// sinc(X_b (x - s)); the symmetry w_{7-s}(x) = w_s(-x) splits them into 4 x 4
+// systems for the even and odd parts, which are solved at kWindowDegree
+// Chebyshev nodes of x^2 and fitted by polynomials in z = 2 x^2 / xm^2 - 1
+// (w = E + x O; in z their terms stay near the size of the weights, while
+// powers of x^2 cancel and would cost two digits in float32).
+// Returns the rms error over x and th, polynomials included.
+struct WindowWeights {
+    double even[kWindowDegree][4], odd[kWindowDegree][4];
+};
+
+double mean_sinc(const std::vector<double>& X, double x) {
+    double s = 0.0;
+    for (double b : X) {
+        const double y = b * x;
+        s += std::fabs(y) < 1e-6 ? 1.0 - y * y / 6.0 : std::sin(y) / y;
+    }
+    return s / static_cast<double>(X.size());
+}
+
+// b = A^-1 b by elimination with row exchanges
+template <int N>
+void solve(double (&A)[N][N], double (&b)[N]) {
+    for (int i = 0; i < N; ++i) {
+        int piv = i;
+        for (int r = i + 1; r < N; ++r)
+            if (std::fabs(A[r][i]) > std::fabs(A[piv][i])) piv = r;
+        for (int c = 0; c < N; ++c) std::swap(A[i][c], A[piv][c]);
+        std::swap(b[i], b[piv]);
+        for (int r = i + 1; r < N; ++r) {
+            const double f = A[r][i] / A[i][i];
+            for (int c = i; c < N; ++c) A[r][c] -= f * A[i][c];
+            b[r] -= f * b[i];
+        }
+    }
+    for (int i = N - 1; i >= 0; --i) {
+        for (int c = i + 1; c < N; ++c) b[i] -= A[i][c] * b[c];
+        b[i] /= A[i][i];
+    }
+}
+
+void window_design(const std::vector<double>& X, double xm, WindowWeights* out) {
+    constexpr int D = kWindowDegree;
+    double g[8];   // mean sinc at whole sample distances
+    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, d);
+    const double ym = xm * xm;
+    double node[D], E[D][4], O[D][4];
+    for (int i = 0; i < D; ++i) {
+        node[i] = std::cos(kPi * (i + 0.5) / D);
+        const double x = std::sqrt(0.5 * (1.0 + node[i]) * ym);
+        double b[8];
+        for (int s = 0; s < 8; ++s) b[s] = mean_sinc(X, x - (s - 3.5));
+        for (int par = 0; par < 2; ++par) {
+            const double sg = par ? -1.0 : 1.0;
+            double A[4][4], r[4];
+            for (int s = 0; s < 4; ++s) {
+                for (int t = 0; t < 4; ++t) A[s][t] = g[std::abs(s - t)] + sg * g[7 - s - t];
+                A[s][s] += 1e-13;   // below the rounding of the FP16 pairs squared
+                r[s] = 0.5 * (b[s] + sg * b[7 - s]);
+            }
+            solve(A, r);
+            for (int s = 0; s < 4; ++s) (par ? O : E)[i][s] = par ? r[s] / x : r[s];
+        }
+    }
+    for (int par = 0; par < 2; ++par)
+        for (int s = 0; s < 4; ++s) {
+            double V[D][D], v[D];
+            for (int i = 0; i < D; ++i) {
+                double pw = 1.0;
+                for (int k = 0; k < D; ++k) V[i][k] = pw, pw *= node[i];
+                v[i] = (par ? O : E)[i][s];
+            }
+            solve(V, v);
+            for (int k = 0; k < D; ++k) (par ? out->odd : out->even)[k][s] = v[k];
+        }
+}
+
+// rms error of these weights over the positions |x| <= xm and the bands X,
+// polynomials included
+double window_error(const std::vector<double>& X, double xm, const WindowWeights& wt) {
+    constexpr int D = kWindowDegree;
+    const double ym = xm * xm;
+    double g[8];
+    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, d);
+    double err = 0.0;
+    constexpr int NX = 9;
+    for (int i = 0; i < NX; ++i) {
+        const double x = xm * (i + 0.5) / NX, z = 2.0 * x * x / ym - 1.0;
+        double w[8], e = 1.0;
+        for (int s = 0; s < 4; ++s) {
+            double ev = 0.0, od = 0.0;
+            for (int k = D - 1; k >= 0; --k) {
+                ev = ev * z + wt.even[k][s];
+                od = od * z + wt.odd[k][s];
+            }
+            w[s] = ev + x * od;
+            w[7 - s] = ev - x * od;
+        }
+        for (int s = 0; s < 8; ++s) {
+            e -= 2.0 * w[s] * mean_sinc(X, x - (s - 3.5));
+            for (int t = 0; t < 8; ++t) e += w[s] * w[t] * g[std::abs(s - t)];
+        }
+        err += std::max(e, 0.0);
+    }
+    return std::sqrt(err / NX);
+}
+
+// The window plan of a whole FP32 call (see k_backproject_window.hip), or
+// false where it does not apply: other precisions, methods or references, an
+// option that asks for a kernel or its shape, an interpolation or an
+// oversampling of the caller's own, or a pixel pitch too coarse for eight
+// samples per 4x4 group.
+//
+// The range step: a group's ranges span at most gspan = 2 |(3 dx, 3 dy)|
+// (|grad l| <= 2); the step is the widest of five (gspan = 3.4 .. 5.66
+// samples) whose estimated interpolation error is smaller than the B-spline's
+// at the caller's oversampling over the same bands: 0.55 of it with even
+// window starts, 0.9 with any start, and 1.5 over the lower half of |k_z|
+// (the B-spline's falls faster towards a band's centre).  At those lines the
+// image's error against float64 is 0.25 .. 0.85 of the B-spline path's over
+// 65 problems of 24 .. 509 scan positions and 2.2 .. 5.6 mm pixels; at 1.3 of
+// the B-spline's estimate it was 0.8 .. 1.9 of it.
+bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPlan& base, HybridPlan* out) {
+    if (base.precision != PL_PREC_FP32 || base.range_method != PL_RANGE_NUFFT || base.ref_mode != PL_REF_BAND_CENTRE ||
+        base.interp != PL_INTERP_BSPLINE4 || base.sigma_l > 6.0 || base.force_tile || base.force_tile_y ||
+        base.force_kpl || base.force_waves || base.force_kb || base.force_bp_mfma)
+        return false;
+    HybridPlan p = base;
+    p.bp_window = true;
+    p.bp_gather = false;
+    p.block = kWindowBins;
+    const int n_lo = (p.n_z + 1) / 2;
+    p.n_blocks = (n_lo + kWindowBins - 1) / kWindowBins;
+    std::vector<double> half(p.n_blocks, 0.0);
+    p.half_band = 0.0;
+    for (int b = 0; b < p.n_blocks; ++b) {
+        // |k_z| of bins m and mirrors n - 1 - m (which is -(m + 1) steps)
+        const int m0 = b * kWindowBins, m1 = std::min(n_lo, m0 + kWindowBins) - 1;
+        const int top = m1 < p.n_z / 2 ? m1 + 1 : m1;
+        double lo = 1e300, hi = -1e300;
+        for (int m = m0; m <= top; ++m) {
+            const double kz = 2.0 * kPi * m / (p.n_z * g->scan_step), q = 0.25 * kz * kz;
+            if (g->k[p.n_f - 1] * g->k[p.n_f - 1] <= q) continue;
+            int f = 0;
+            while (g->k[f] * g->k[f] <= q) ++f;
+            lo = std::min(lo, std::sqrt(g->k[f] * g->k[f] - q));
+            hi = std::max(hi, std::sqrt(g->k[p.n_f - 1] * g->k[p.n_f - 1] - q));
+        }
+        p.kref[b] = hi < lo ? 0.0 : 0.5 * (lo + hi);
+        half[b] = hi < lo ? 0.0 : 0.5 * (hi - lo);
+        p.half_band = std::max(p.half_band, half[b]);
+    }
+    if (!(p.half_band > 0)) return false;   // one frequency, no k_z spread
+    if (p.half_band * std::hypot(3.0 * grid->dx, 3.0 * grid->dy) * 2.0 / 5.66 > 1.1) return false;   // far over the bound
+    // the B-spline's error, sqrt(2) (k' du / 2 pi)^4 at k': over all bands,
+    // and over the lower half of |k_z|, where a scene's echo is strongest
+    const int n_low = (p.n_blocks + 1) / 2;
+    double base_err = 0.0, base_low = 0.0;
+    for (int b = 0; b < p.n_blocks; ++b) {
+        const double e2 = 2.0 * std::pow(half[b] * base.du / (2.0 * kPi), 8) / 9.0;
+        base_err += e2;
+        if (b < n_low) base_low += e2;
+    }
+    base_err = std::sqrt(base_err / p.n_blocks);
+    base_low = std::sqrt(base_low / n_low);
+
+    const double gspan = std::hypot(3.0 * grid->dx, 3.0 * grid->dy) * 2.0;
+    const double spans[5] = {3.4, 3.77, 4.25, 4.85, 5.66};
+    WindowWeights w;
+    bool found = false;
+    for (int step = 2; step >= 1 && !found; --step)
+        for (int i = 0; i < 5 && !found; ++i) {
+            p.win_step = step;
+            p.win_span = spans[i];
+            p.du = gspan / spans[i];
+            p.sigma_used = kPi / (p.half_band * p.du);
+            if (p.sigma_used < 1.3) continue;
+            std::vector<double> X;
+            for (double h : half) X.push_back(h * p.du);
+            // positions: half the span, half a step of the window's start, and
+            // 1/64 sample and float rounding of the group's lowest position
+            const double xm = 0.5 * (spans[i] + step) + 0.02;
+            p.win_z = 2.0 / (xm * xm);
+            window_design(X, xm, &w);
+            found = window_error(X, xm, w) <= (step == 2 ? 0.55 : 0.9) * base_err &&
+                    window_error({X.begin(), X.begin() + n_low}, xm, w) <= 1.5 * base_low;
+        }
+    if (!found) return false;
+    for (int k = 0; k < kWindowDegree; ++k)
+        for (int s = 0; s < 4; ++s) {
+            p.win_even[k][s] = static_cast<float>(w.even[k][s]);
+            p.win_odd[k][s] = static_cast<float>(w.odd[k][s]);
+        }
+
+    // staged rows: every group's window of a 16x16 tile, from a start on a
+    // multiple of four samples (the tile table's window start)
+    p.tile_x = p.tile_y = 16;
+    p.tiles_x = (p.nx + 15) / 16;
+    p.tiles_y = (p.ny + 15) / 16;
+    p.waves = 4;
+    const double reach = 2.0 * std::hypot(15.0 * grid->dx, 15.0 * grid->dy) / p.du;
+    const int lead = p.win_step == 2 ? 2 : 0;   // half the rows are staged from two samples earlier
+    const int chunks = std::max(8, (static_cast<int>(std::ceil(reach - p.win_span + 9.2 + p.win_step)) + 3 + lead + 3) / 4);
+    if (chunks > 9) return false;
+    p.window = 4 * chunks;
+    p.window_pad = 2 * chunks + 1;
+    // eight samples beyond the image's ranges on both sides (the windows of
+    // groups that reach past the image's edge), and four before the first
+    // staged row
+    p.lo_margin = 12;
+    p.n_l = std::max(static_cast<int>(std::ceil(p.span / p.du)) + 21, p.window + 4);
+    p.n_l = (p.n_l + 3) & ~3;
+    const int want = static_cast<int>(std::ceil(kNufftUpsample * p.n_l));
+    p.n_fine = 0;
+    for (int r = std::max(2, (want + 63) / 64); r <= 32 && !p.n_fine; ++r)
+        if (is_fft_friendly(r)) p.n_fine = 64 * r;
+    if (!p.n_fine || static_cast<unsigned long long>(p.n_z) * p.n_l * 8 >= (1ull << 31)) return false;
+    factor_radices(p.n_fine, &p.fine_rad);
+    if (set_spreading(&p, p.sigma_used)) return false;
+    // |q| <= n_f k_max sqrt(2) (largest |S| part), a tenth for the NUFFT's error
+    p.log2_gain = static_cast<int>(std::ceil(std::log2(1.6 * p.n_f * g->k[p.n_f - 1])));
+
+    // split items' partial spectra: as many pieces as the tail split can ask
+    // for, within what the workspace of make_plan's plan or the static
+    // scratch holds already where that is the limit
+    p.part_pieces = 0;
+    if (set_layout(&p)) return false;
+    const long long items = static_cast<long long>(p.tiles_x) * p.tiles_y * p.n_blocks;
+    long long pieces = std::min<long long>(kMaxWindowPieces, items * ((p.n_ch + 1) / 2));
+    const size_t scratch = static_cast<size_t>(PL_STATIC_SCRATCH_BYTES);
+    if (base.total <= scratch) {
+        if (p.total > scratch) return false;
+        pieces = std::min<long long>(pieces, (scratch - p.total) / kWindowPieceBytes);
+    }
+    p.part_pieces = static_cast<int>(pieces);
+    if (set_layout(&p)) return false;
+    *out = p;
+    return true;
 }
 
 }  // namespace
@@ -285,6 +597,8 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
         span = std::max(span, lmax - lmin);
     }
 
+    p.span = span;
+
     // k_z-per-lane kernel tile: the staged range window must hold every tap
     // of the tile's pixels (|l(p) - l(centre)| <= 2 * half-diagonal).  Prefer
     // the largest tile whose window fits 64 samples (one staging load per
@@ -363,26 +677,7 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
         for (int b = 0; b < p.n_blocks; ++b) p.kref[b] = p.dkl * std::nearbyint(p.kref[b] / p.dkl);
     }
 
-    // Exponential-of-semicircle kernel exp(beta (sqrt(1 - z^2) - 1)) of
-    // width W (Barnett, Magland, af Klinteberg 2019).  For the 2x fine grid:
-    // W = ceil(log10(1/tol)) + 1, beta = 2.30 W.  For an upsampling factor
-    // s = n_fine / n_l below 2, their error estimate exp(-pi W sqrt(1 - 1/s))
-    // gives W = ceil(ln(1/tol) / (pi sqrt(1 - 1/s))), and beta =
-    // 0.97 pi W (1 - 1/(2 s)).
-    const double ups = static_cast<double>(p.n_fine) / p.n_l;
-    if (ups >= 1.999) {
-        p.W = std::max(2, static_cast<int>(std::ceil(std::log10(1.0 / p.tol))) + 1);
-        p.W = std::min(p.W, 16);
-        p.beta = 2.30 * p.W;
-    } else {
-        p.W = std::max(2, static_cast<int>(std::ceil(std::log(1.0 / p.tol) / (kPi * std::sqrt(1.0 - 1.0 / ups)))));
-        p.W = std::min(p.W, 16);
-        p.beta = 0.97 * kPi * p.W * (1.0 - 0.5 / ups);
-    }
-    p.h = 0.5 * p.W;
-    if (p.n_fine / p.sigma_l + 2 * p.W + 2 >= p.n_fine) return fail(PL_EUNSUPPORTED, "fine grid too short");
-    p.n_gl = std::min(kMaxGL, 4 * p.W + 16);
-    gauss_legendre(p.n_gl, p.gl_x, p.gl_w);
+    if (int rc = set_spreading(&p, p.sigma_l)) return rc;
 
     // interpolation weights as cubic polynomials in t = u - floor(u), taps at
     // floor(u) - 1 .. floor(u) + 2
@@ -398,42 +693,19 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
     const float(*src)[4] = p.interp == PL_INTERP_BSPLINE4 ? bsp : (p.interp == PL_INTERP_LAGRANGE4 ? lag : lin);
     std::memcpy(p.coef, src, sizeof(p.coef));
 
-    // workspace layout
-    const size_t nch = p.n_ch, nz = p.n_z, nf = p.n_f, npix = static_cast<size_t>(p.nx) * p.ny;
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        const size_t o = off;
-        off = align256(off + bytes);
-        return o;
-    };
-    p.off_spec = take(nch * nz * nf * 8);
-    p.off_q = take(nch * nz * static_cast<size_t>(p.n_l) * 8);
-    p.off_G = take(npix * nz * 8);
-    p.off_llo = take(nch * 8);
-    p.off_lref = take(nch * 8);
-    p.off_zfft = take(p.zfft.bytes);
-    p.off_tw_fine = take(static_cast<size_t>(p.n_fine) * 8);
-    p.off_deap = take(static_cast<size_t>(p.n_l) * 4);
-    p.off_kp = take(nz * nf * 8);
-    p.off_wk = take(nz * nf * 4);
-    p.off_krz = take(nz * 8);
-    p.off_tiles = take(tile_table_bytes(p));
-    p.off_part = take(backproject_mfma_part_bytes(p));
-    p.n_chp = (p.n_ch + 31) / 32 * 32;
-    p.n_fp = (p.n_f + 15) / 16 * 16;
-    if (p.precision != PL_PREC_FP32) {
-        if (p.n_fp > 128)
-            return fail(PL_EUNSUPPORTED, "MFMA range compression supports up to 128 frequencies");
-        p.off_mfma_a = take(nz * static_cast<size_t>(p.n_chp) * 4);
-        p.off_qexp = take(4 * (kProfileScaleParts + 1));
-        p.off_mfma_b = take(nz * static_cast<size_t>(p.n_chp) * 4 * p.n_fp * 2);
-    } else {
-        p.off_mfma_a = off;
-        p.off_mfma_b = off;
-        p.off_qexp = off;
-    }
-    p.total = off;
+    if (int rc = set_layout(&p)) return rc;
+    p.need = p.total;
     *out = p;
+    return PL_OK;
+}
+
+int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* out) {
+    if (int rc = make_plan(g, grid, opts, out)) return rc;
+    HybridPlan w;
+    if (window_plan(g, grid, *out, &w)) {
+        w.need = std::max(w.total, out->total);
+        *out = w;
+    }
     return PL_OK;
 }
 
@@ -441,23 +713,26 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
 static_assert(sizeof(pl_image_grid) == 2 * sizeof(int32_t) + 4 * sizeof(double), "padding in pl_image_grid");
 static_assert(sizeof(pl_hybrid_opts) == 10 * sizeof(int32_t) + 2 * sizeof(double), "padding in pl_hybrid_opts");
 
-int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* out) {
-    if (!g || !grid || !out) return make_plan(g, grid, opts, out);   // its error
+int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, bool whole,
+                HybridPlan* out) {
+    auto plan = [&] { return whole ? make_call_plan(g, grid, opts, out) : make_plan(g, grid, opts, out); };
+    if (!g || !grid || !out) return plan();                         // its error
     const pl_hybrid_opts key = opts ? *opts : pl_hybrid_opts{};     // no options: all zero
     {
         std::lock_guard<std::mutex> lock(g->plan_mu);
         for (const auto& c : g->plans)
-            if (!std::memcmp(&c.grid, grid, sizeof(*grid)) && !std::memcmp(&c.opts, &key, sizeof(key))) {
+            if (c.whole == whole && !std::memcmp(&c.grid, grid, sizeof(*grid)) &&
+                !std::memcmp(&c.opts, &key, sizeof(key))) {
                 *out = c.plan;
                 return PL_OK;
             }
     }
-    if (int rc = make_plan(g, grid, opts, out)) return rc;   // outside the lock; errors are not kept
+    if (int rc = plan()) return rc;   // outside the lock; errors are not kept
     std::lock_guard<std::mutex> lock(g->plan_mu);
     if (g->plans.size() < pl_geometry::kPlanCache) {
-        g->plans.push_back({*grid, key, *out});
+        g->plans.push_back({*grid, key, whole, *out});
     } else {
-        g->plans[g->next_plan] = {*grid, key, *out};
+        g->plans[g->next_plan] = {*grid, key, whole, *out};
         g->next_plan = (g->next_plan + 1) % pl_geometry::kPlanCache;
     }
     return PL_OK;

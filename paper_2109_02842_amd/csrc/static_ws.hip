@@ -47,13 +47,13 @@ extern "C" int reconstruct_hybrid_static(const pl_geometry* g, const pl_image_gr
     clear_error();
     if (!g || !grid || !echo || !image) return fail(PL_EINVAL, "reconstruct_hybrid_static: null argument");
     HybridPlan p;
-    int rc = cached_plan(g, grid, opts, &p);
+    int rc = cached_plan(g, grid, opts, true, &p);
     if (rc) return rc;
-    if (p.total > static_cast<size_t>(PL_STATIC_SCRATCH_BYTES))
+    if (p.need > static_cast<size_t>(PL_STATIC_SCRATCH_BYTES))
         return fail(PL_EWORKSPACE,
                     "reconstruct_hybrid_static: this problem needs %zu bytes of workspace, the static scratch "
                     "holds %zu (use reconstruct_hybrid with a workspace)",
-                    p.total, static_cast<size_t>(PL_STATIC_SCRATCH_BYTES));
+                    p.need, static_cast<size_t>(PL_STATIC_SCRATCH_BYTES));
     void* ws = nullptr;
     if ((rc = scratch_address(&ws))) return rc;
     return reconstruct_impl(g, grid, opts, echo, image, ws, PL_STATIC_SCRATCH_BYTES, nullptr, stream, true, false,
