@@ -295,6 +295,8 @@ struct BatchScanDesc {
 
 constexpr int kGatherWaves = 4;   // wavefronts per workgroup
 constexpr int kGatherBatch = 4;   // channels per weight batch
+constexpr int kSubRows = 8;       // k_z rows per workgroup of the row-split form
+constexpr int kSubBatch = 8;      // and its channels per step
 
 typedef __attribute__((address_space(3))) unsigned char* lds_bytes_t;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -307,6 +309,75 @@ typedef const GatherTileEntry* const_tile_t;
 typedef const float2* const_f2_t;
 #define PL_LDS_COPY16(RS, DST, VOFF) ((void)(RS), (void)(DST), (void)(VOFF))
 #endif
+
+// A lane's pixel of an 8x8 tile, and its weights for a channel.
+struct GatherPixel {
+    int x, y, wpl;
+    bool valid;
+    float ox, oy, oo, inv_du, kref_rev;
+    __device__ __forceinline__ GatherPixel(const BpgArgs& a, int tx0, int ty0, int lane, int blk) {
+        x = tx0 + (lane & 7);
+        y = ty0 + (lane >> 3);
+        wpl = 2 * a.nchk;
+        valid = x < a.nx && y < a.ny;
+        // the offset from the tile centre
+        ox = ((lane & 7) - 3.5f) * static_cast<float>(a.dx);
+        oy = ((lane >> 3) - 3.5f) * static_cast<float>(a.dy);
+        oo = fmaf(ox, ox, oy * oy);
+        inv_du = static_cast<float>(a.inv_du);
+        kref_rev = static_cast<float>(a.kref[blk] * (0.5 / kPi));
+    }
+    // The four tap weights, carrier and byte offset of the first tap in the
+    // row.  Lanes of pixels outside the image compute them like the others
+    // (their offset is clamped into the row; their sums are never written); a
+    // channel past the last one is never read.  Multiply-adds are spelled
+    // out: every kernel that shares this gives the same bits.
+    __device__ __forceinline__ void weights(const BpgArgs& a, const GatherTileEntry& e, float2 c0,
+                                            float4* __restrict__ slot) const {
+        // range offset from the tile centre (see GatherTileEntry)
+        const float sT = fmaf(2.f, fmaf(e.xt, ox, e.yt * oy), oo);
+        float dl = sT * __builtin_amdgcn_rcpf(e.dt + __builtin_amdgcn_sqrtf(fmaf(e.dt, e.dt, sT)));
+        if (a.mono) {
+            dl += dl;
+        } else {
+            const float sR = fmaf(2.f, fmaf(e.xr, ox, e.yr * oy), oo);
+            dl = fmaf(sR, __builtin_amdgcn_rcpf(e.dr + __builtin_amdgcn_sqrtf(fmaf(e.dr, e.dr, sR))), dl);
+        }
+        const float uu = fmaf(dl, inv_du, e.uf);
+        const float fv = floorf(uu);
+        const float t = uu - fv;
+        // within the window by the bound above; the clamp keeps every read
+        // inside the staged row whatever the rounding
+        const int i0 = max(0, min(e.base + static_cast<int>(fv), wpl - 4));
+        float w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            w[j] = fmaf(fmaf(fmaf(a.coef[j][3], t, a.coef[j][2]), t, a.coef[j][1]), t, a.coef[j][0]);
+        // carrier exp(j k_ref l): the centre's (tile table) times the offset's
+        const float2 c1 = cis_rev_f(kref_rev * dl);   // |dl| spans a tile: a few revolutions
+        slot[0] = make_float4(w[0], w[1], w[2], w[3]);
+        slot[64] = make_float4(fmaf(c0.x, c1.x, -(c0.y * c1.y)), fmaf(c0.x, c1.y, c0.y * c1.x), __int_as_float(i0 * 8), 0.f);
+    }
+};
+
+// One (pixel, k_z, channel) term: four taps at p, weights wa, carrier wb.xy.
+__device__ __forceinline__ void gather_term(const unsigned char* p, const float4& wa, const float4& wb, float2& acc) {
+    const float2* cp = reinterpret_cast<const float2*>(p);
+    // four separate 8-byte reads: the empty asm keeps the compiler from
+    // pairing them into ds_read2_b64
+    float2 q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        q[j] = cp[j];
+        asm volatile("" ::: "memory");
+    }
+    const float re = fmaf(wa.w, q[3].x, fmaf(wa.z, q[2].x, fmaf(wa.y, q[1].x, wa.x * q[0].x)));
+    const float im = fmaf(wa.w, q[3].y, fmaf(wa.z, q[2].y, fmaf(wa.y, q[1].y, wa.x * q[0].y)));
+    acc.x = fmaf(wb.x, re, acc.x);
+    acc.x = fmaf(-wb.y, im, acc.x);
+    acc.y = fmaf(wb.x, im, acc.y);
+    acc.y = fmaf(wb.y, re, acc.y);
+}
 
 // RSC 16-byte chunks per LDS row, of which nchk (the window) are staged.
 // With A, B = (l_c -+ reach - l_lo) / du for the tile centre's range l_c,
@@ -340,9 +411,6 @@ __device__ __forceinline__ void gather_tile(const BpgArgs& a, const float2* __re
     const int tx0 = (tile % a.tiles_x) * 8, ty0 = (tile / a.tiles_x) * 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wpl = 2 * a.nchk;
-    const float kref_rev_f = static_cast<float>(a.kref[blk] * (0.5 / kPi));
-    const float inv_du_f = static_cast<float>(a.inv_du);
     const GatherTileEntry* tt = tab + static_cast<size_t>(tile) * a.n_ch;
     const float2* tc = reinterpret_cast<const float2*>(tab + static_cast<size_t>(a.n_tiles) * a.n_ch) +
                        (static_cast<size_t>(blk) * a.n_tiles + tile) * a.n_ch;
@@ -373,45 +441,11 @@ __device__ __forceinline__ void gather_tile(const BpgArgs& a, const float2* __re
         }
     };
 
-    // this lane's pixel and its offset from the tile centre
-    const int px = tx0 + (lane & 7), py = ty0 + (lane >> 3);
-    const bool pvalid = px < a.nx && py < a.ny;
-    const float ox = ((lane & 7) - 3.5f) * static_cast<float>(a.dx), oy = ((lane >> 3) - 3.5f) * static_cast<float>(a.dy);
-    const float oo = ox * ox + oy * oy;
-
-    // weights of (this lane's pixel, channel c) into slot [wave]: four tap
-    // weights, carrier, byte offset of the first tap in the row.  Lanes of
-    // pixels outside the image compute them like the others (their offset
-    // is clamped into the row; their sums are never written); a channel past
-    // the last one is never read.
+    // weights of (this lane's pixel, channel c) into slot [wave]
+    const GatherPixel px(a, tx0, ty0, lane, blk);
     auto weights = [&](int c) {
         const int ce = min(c, a.n_ch - 1);
-        const GatherTileEntry e = ttc[ce];
-        // range offset from the tile centre (see GatherTileEntry)
-        const float sT = 2.f * (e.xt * ox + e.yt * oy) + oo;
-        float dl = sT * __builtin_amdgcn_rcpf(e.dt + __builtin_amdgcn_sqrtf(e.dt * e.dt + sT));
-        if (a.mono) {
-            dl += dl;
-        } else {
-            const float sR = 2.f * (e.xr * ox + e.yr * oy) + oo;
-            dl += sR * __builtin_amdgcn_rcpf(e.dr + __builtin_amdgcn_sqrtf(e.dr * e.dr + sR));
-        }
-        const float uu = e.uf + dl * inv_du_f;
-        const float fv = floorf(uu);
-        const float t = uu - fv;
-        // within the window by the bound above; the clamp keeps every read
-        // inside the staged row whatever the rounding
-        const int i0 = max(0, min(e.base + static_cast<int>(fv), wpl - 4));
-        float w[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            w[j] = ((a.coef[j][3] * t + a.coef[j][2]) * t + a.coef[j][1]) * t + a.coef[j][0];
-        // carrier exp(j k_ref l): the centre's (tile table) times the offset's
-        const float2 c0 = tcc[ce];
-        const float2 c1 = cis_rev_f(kref_rev_f * dl);   // |dl| spans a tile: a few revolutions
-        float4* slot = wts + wave * 2 * 64 + lane;
-        slot[0] = make_float4(w[0], w[1], w[2], w[3]);
-        slot[64] = make_float4(c0.x * c1.x - c0.y * c1.y, c0.x * c1.y + c0.y * c1.x, __int_as_float(i0 * 8), 0.f);
+        px.weights(a, ttc[ce], tcc[ce], wts + wave * 2 * 64 + lane);
     };
 
     float2 acc[RW];
@@ -444,30 +478,14 @@ __device__ __forceinline__ void gather_tile(const BpgArgs& a, const float2* __re
             const unsigned off = __float_as_uint(wb.z);
             const unsigned char* rp = smem + lds_q + (cc & 1) * kBufBytes + row0 + off;
 #pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const float2* cp = reinterpret_cast<const float2*>(rp + r * RSC * 16);
-                // four separate 8-byte reads: the empty asm keeps the
-                // compiler from pairing them into ds_read2_b64
-                float2 q[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    q[j] = cp[j];
-                    asm volatile("" ::: "memory");
-                }
-                const float re = wa.x * q[0].x + wa.y * q[1].x + wa.z * q[2].x + wa.w * q[3].x;
-                const float im = wa.x * q[0].y + wa.y * q[1].y + wa.z * q[2].y + wa.w * q[3].y;
-                acc[r].x = fmaf(wb.x, re, acc[r].x);
-                acc[r].x = fmaf(-wb.y, im, acc[r].x);
-                acc[r].y = fmaf(wb.x, im, acc[r].y);
-                acc[r].y = fmaf(wb.y, re, acc[r].y);
-            }
+            for (int r = 0; r < RW; ++r) gather_term(rp + r * RSC * 16, wa, wb, acc[r]);
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         }
     }
 
-    if (pvalid) {
-        float2* out = G + (static_cast<size_t>(py) * a.nx + px) * a.n_z;
+    if (px.valid) {
+        float2* out = G + (static_cast<size_t>(px.y) * a.nx + px.x) * a.n_z;
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
             const int kz = blk * KB + wave * RW + r;
@@ -485,6 +503,125 @@ __global__ __launch_bounds__(64 * kGatherWaves) void backproject_gather_kernel(c
     if (work >= a.n_work) return;  // workgroup-uniform, before any barrier
     const int blk = work / a.n_tiles;
     gather_tile<KB, RSC>(a, q, tab, G, blk, work - blk * a.n_tiles, smem);
+}
+
+// Eight k_z rows per workgroup, for calls whose (k_z block, tile) items leave
+// most CUs idle.  There the form above is a serial chain, one copy's latency
+// and one barrier per channel; here eight channels are staged per step (two
+// steps' rows and weight slots in LDS, one workgroup per CU), one barrier per
+// step, and a channel's rows are spread over more workgroups.  The terms are
+// gather_tile's, in its order: same bits.  Measured, whole calls of 120
+// channels on 32x32 pixels x 32 k_z (16 items): 132 -> 88 us, four channels
+// per step and entries read in their own step 111.
+template <int RSC>
+__global__ __launch_bounds__(64 * kGatherWaves) void backproject_gather_rows_kernel(
+    const float2* __restrict__ q, const GatherTileEntry* __restrict__ tab, BpgArgs a, int kb,
+    float2* __restrict__ G) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int NW = kGatherWaves, NB = kSubBatch, RW = kSubRows / NW, PW = NB / NW;
+    constexpr int NI = NB * kSubRows * RSC / 64, NIW = (NI + NW - 1) / NW;   // copy instructions per step
+    constexpr unsigned kRowBytes = NB * kSubRows * RSC * 16, kSlotBytes = NB * 2 * 64 * 16;
+    static_assert(kSubRows % NW == 0 && NB % NW == 0 && NB * kSubRows * RSC % 64 == 0, "whole copies and shares");
+    const int work = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+    if (work >= a.n_work) return;   // workgroup-uniform, before any barrier
+    const int subs = kb / kSubRows;
+    const int tile = work % a.n_tiles, rest = work / a.n_tiles;
+    const int blk = rest / subs, kz0 = blk * kb + (rest - blk * subs) * kSubRows;
+    const int tx0 = (tile % a.tiles_x) * 8, ty0 = (tile / a.tiles_x) * 8;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (kz0 >= a.n_z) return;   // workgroup-uniform: rows past the last bin
+    const GatherTileEntry* tt = tab + static_cast<size_t>(tile) * a.n_ch;
+    const float2* tc = reinterpret_cast<const float2*>(tab + static_cast<size_t>(a.n_tiles) * a.n_ch) +
+                       (static_cast<size_t>(blk) * a.n_tiles + tile) * a.n_ch;
+    const GatherPixel px(a, tx0, ty0, lane, blk);
+
+    // all profiles under one descriptor (below 2 GiB, checked on the host);
+    // a lane's chunk belongs to one channel of the step and one row
+    const __amdgpu_buffer_rsrc_t rs =
+        slab_rsrc(q, static_cast<unsigned>(static_cast<size_t>(a.n_ch) * a.n_z * a.n_l * 8));
+    unsigned doff[NIW];
+    int dch[NIW];
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) {
+        const int g = (wave + NW * j) * 64 + lane;
+        const int r = g / RSC, k = g - r * RSC;
+        const int kz = min(kz0 + r % kSubRows, a.n_z - 1);
+        dch[j] = min(r / kSubRows, NB - 1);
+        doff[j] = (r < NB * kSubRows && k < a.nchk) ? static_cast<unsigned>((kz * a.n_l + 2 * k) * 8) : 0x80000000u;
+    }
+    const unsigned chan_bytes = static_cast<unsigned>(a.n_z) * a.n_l * 8u;
+    // the step's table entries are read a step before they are used: one
+    // table latency less per step.  A lane needs the window starts of its
+    // own chunks' channels, a wavefront the entries of its PW channels.
+    int win[NIW];
+    GatherTileEntry ent[PW];
+    float2 car[PW];
+    auto entries = [&](int c0) {
+#pragma unroll
+        for (int j = 0; j < NIW; ++j) win[j] = tt[min(c0 + dch[j], a.n_ch - 1)].win;
+#pragma unroll
+        for (int k = 0; k < PW; ++k) {
+            const int c = min(c0 + wave + NW * k, a.n_ch - 1);
+            ent[k] = tt[c];
+            car[k] = tc[c];
+        }
+    };
+    auto stage = [&](int c0, int buf) {
+        const lds_bytes_t dst = (lds_bytes_t)(smem + 2 * kSlotBytes + buf * kRowBytes);
+#pragma unroll
+        for (int j = 0; j < NIW; ++j)
+            if (wave + NW * j < NI) {
+                const unsigned b = min(c0 + dch[j], a.n_ch - 1) * chan_bytes + 8u * static_cast<unsigned>(win[j]);
+                PL_LDS_COPY16(rs, dst + (wave + NW * j) * 1024, doff[j] == 0x80000000u ? doff[j] : doff[j] + b);
+            }
+    };
+    auto weights = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < PW; ++k)
+            px.weights(a, ent[k], car[k],
+                       reinterpret_cast<float4*>(smem + buf * kSlotBytes) + (wave + NW * k) * 2 * 64 + lane);
+    };
+
+    float2 acc[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) acc[r] = make_float2(0.f, 0.f);
+    entries(0);
+    stage(0, 0);
+    weights(0);
+    entries(NB);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    int buf = 0;
+#pragma unroll 1
+    for (int c0 = 0; c0 < a.n_ch; c0 += NB) {
+        if (c0 + NB < a.n_ch) {
+            stage(c0 + NB, buf ^ 1);
+            weights(buf ^ 1);
+            entries(c0 + 2 * NB);
+        }
+#pragma unroll
+        for (int cc = 0; cc < NB; ++cc) {
+            if (c0 + cc >= a.n_ch) break;
+            const float4* slot = reinterpret_cast<const float4*>(smem + buf * kSlotBytes) + cc * 2 * 64 + lane;
+            const float4 wa = slot[0], wb = slot[64];
+            const unsigned char* rp = smem + 2 * kSlotBytes + buf * kRowBytes +
+                                      (cc * kSubRows + wave * RW) * RSC * 16 + __float_as_uint(wb.z);
+#pragma unroll
+            for (int r = 0; r < RW; ++r) gather_term(rp + r * RSC * 16, wa, wb, acc[r]);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        buf ^= 1;
+    }
+    if (px.valid) {
+        float2* out = G + (static_cast<size_t>(px.y) * a.nx + px.x) * a.n_z;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const int kz = kz0 + wave * RW + r;
+            if (kz < a.n_z) out[kz] = acc[r];
+        }
+    }
 }
 
 struct TileTableArgs {
@@ -594,6 +731,29 @@ int launch_gather(const BpgArgs& a, size_t smem, unsigned blocks, hipStream_t s,
     return check_launch("back-projection (pixel per lane)");
 }
 
+template <int RSC>
+int launch_gather_rows(const BpgArgs& a, int kb, hipStream_t s, const float2* q, const GatherTileEntry* tab,
+                       float2* G) {
+    auto fn = backproject_gather_rows_kernel<RSC>;
+    const size_t smem = 2ull * kSubBatch * 2 * 64 * 16 + 2ull * kSubBatch * kSubRows * RSC * 16;
+    if (smem > 65536) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem));
+        if (e != hipSuccess) return fail(PL_EDEVICE, "back-projection LDS of %zu bytes: %s", smem, hipGetErrorString(e));
+    }
+    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(8 * a.per_xcd)), dim3(64 * kGatherWaves), smem, s, q, tab, a, kb, G);
+    return check_launch("back-projection (pixel per lane, split rows)");
+}
+
+// Row-split form: up to one item per CU.  Whole calls of 120 channels, one
+// workgroup per item against split rows: 16 items 132 / 88 us, 72 items 140 /
+// 93, 144 items 152 / 136, 256 items 147 / 135, 320 items 161 / 178, 512 items
+// 168 / 217.  Its copies address all profiles by 32-bit offsets, with
+// 0x80000000 for no chunk.
+bool gather_by_rows(const HybridPlan& p, const BpgArgs& a) {
+    return a.n_work <= 256 && static_cast<unsigned long long>(p.n_ch) * p.n_z * p.n_l * 8 < (1ull << 31);
+}
+
 BpgArgs gather_args(const HybridPlan& p) {
     BpgArgs a{};
     a.n_ch = p.n_ch;
@@ -658,6 +818,15 @@ int run_gather(const HybridPlan& p, const DeviceTables& dt, const float2* q, cha
     const unsigned blocks = static_cast<unsigned>(8 * a.per_xcd);
     const GatherTileEntry* tab = reinterpret_cast<const GatherTileEntry*>(ws + p.off_tiles);
     (void)dt;
+    if (gather_by_rows(p, a)) {
+        BpgArgs r = a;
+        r.n_work = a.n_work * (p.block / kSubRows);
+        r.per_xcd = (r.n_work + 7) / 8;
+#define PL_GR(KB, RSC) \
+        if (KB == 32 && p.window_pad == RSC) return launch_gather_rows<RSC>(r, p.block, s, q, tab, G);
+        PL_GATHER_CLASSES(PL_GR)
+#undef PL_GR
+    }
 #define PL_G(KB, RSC) \
     if (p.block == KB && p.window_pad == RSC) return launch_gather<KB, RSC>(a, smem, blocks, s, q, tab, G);
     PL_GATHER_CLASSES(PL_G)
