@@ -277,6 +277,10 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     }
     base_err = std::sqrt(base_err / p.n_blocks);
     base_low = std::sqrt(base_low / n_low);
+    // Where the B-spline itself is off by about its largest estimate (2.3e-5,
+    // a block as wide as the band of k', scans of up to some 70 positions) the
+    // two forms' images would differ by more than 2e-5: the vector kernels stay.
+    if (base_low > 1.6e-5 || base_err > 1.9e-5) return false;
 
     const double gspan = std::hypot(3.0 * grid->dx, 3.0 * grid->dy) * 2.0;
     const double spans[5] = {3.4, 3.77, 4.25, 4.85, 5.66};

@@ -52,8 +52,8 @@ def grid(nx, ny, d):
     return W.ImageGrid(nx=nx, ny=ny, x0=-d * (nx - 1) / 2 + 0.004, y0=-d * (ny - 1) / 2 - 0.003, dx=d, dy=d)
 
 
-MONO = replace(W.C1.array, n_scan=53, n_elem=17, n_freq=20)          # 51 channels: a lone last one
-MULTI = W.ArrayDesc(mode="multi", n_chords=3, radius=0.5, n_elem=11, spacing=W._D_MULTI, n_tx=2, n_scan=70,
+MONO = replace(W.C1.array, n_scan=229, n_elem=17, n_freq=20)          # 51 channels: a lone last one
+MULTI = W.ArrayDesc(mode="multi", n_chords=3, radius=0.5, n_elem=11, spacing=W._D_MULTI, n_tx=2, n_scan=230,
                     scan_step=0.005, n_freq=16, f_start=26e9, f_stop=34e9)   # 66 channels
 
 # (array, grid): partial tiles and pixel groups, odd scan lengths (rows without
@@ -63,7 +63,7 @@ CASES = {
     "mono-fine": (MONO, grid(45, 29, 0.0026)),
     "mono-coarse": (MONO, grid(45, 29, 0.0046)),
     "mono-1x1": (MONO, grid(1, 1, 0.003)),
-    "mono-129": (replace(MONO, n_scan=129), grid(17, 33, 0.003)),
+    "mono-331": (replace(MONO, n_scan=331), grid(17, 33, 0.003)),
     "multi-fine": (MULTI, grid(27, 35, 0.0024)),
     "multi-coarse": (MULTI, grid(15, 50, 0.0038)),
 }
