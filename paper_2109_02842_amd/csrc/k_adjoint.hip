@@ -180,8 +180,17 @@ int launch_range_adjoint_wave(const HybridPlan& p, const float2* qt, char* ws, f
 // register-indexed update per sample it reaches, not four per pixel.  The
 // four wavefronts' copies are summed through LDS in a fixed order, so the
 // result is the same bit for bit on every run.
+//
+// Bound by VALU issue (91 % of the cycles, 27 instructions per pixel and
+// wavefront, of which 12 are the term's, 5 the window's moves, 10 the tile's
+// records and the tile list).  Ranks are read from lanes, not broadcast
+// through LDS, and a monostatic range takes one float64 root: 3.48 -> 3.20 ms
+// for the image of 256 x 128x128 voxels and 320 channels at 4 wavefronts per
+// SIMD; at 3 (129 registers) 3.83.  Two bins per lane (half the records, 224
+// registers, 2 wavefronts) took 5.0 ms; accumulators kept by sample mod 4
+// instead of moved need selects that cost more than the moves.
 struct AdjArgs {
-    int n_ch, n_z, n_l, nx, ny, tiles_x, n_tiles, n_seg, n_work, per_xcd, block;
+    int n_ch, n_z, n_l, nx, ny, tiles_x, n_tiles, n_seg, n_work, per_xcd, block, mono;
     double x0, y0, dx, dy, inv_du;
     float coef[4][4];
     double kref[kMaxBlocks];
@@ -194,6 +203,7 @@ constexpr int kAdjBins = 64;   // k_z bins per workgroup, one per lane
 // G~ through a buffer descriptor: the pixel's row offset is scalar, the
 // lane's bin a fixed per-lane offset, and a lane past the last bin reads
 // beyond the descriptor (zero) instead of branching.
+typedef float adj_seg __attribute__((ext_vector_type(kAdjSeg)));   // registers, also under a uniform index
 typedef unsigned int adj_u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t adj_rsrc(const float2* p, unsigned bytes) {
     const unsigned long long a = reinterpret_cast<unsigned long long>(p);
@@ -208,7 +218,7 @@ __device__ __forceinline__ double rect_dist(double px, double py, double x0, dou
     return sqrt((px - cx) * (px - cx) + (py - cy) * (py - cy));
 }
 
-__global__ __launch_bounds__(64 * kAdjWaves) void backproject_adjoint_kernel(const float2* __restrict__ Gt,
+__global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(4))) void backproject_adjoint_kernel(const float2* __restrict__ Gt,
                                                                            const double* __restrict__ chan,
                                                                            const double* __restrict__ llo,
                                                                            AdjArgs a, float2* __restrict__ qt) {
@@ -249,9 +259,7 @@ __global__ __launch_bounds__(64 * kAdjWaves) void backproject_adjoint_kernel(con
 
     // the lane's copy of the segment, real and imaginary parts apart (each
     // array stays in registers under a wavefront-uniform index)
-    float acr[S], aci[S];
-#pragma unroll
-    for (int i = 0; i < S; ++i) acr[i] = aci[i] = 0.f;
+    adj_seg acr = 0.f, aci = 0.f;
 
 #pragma unroll 1
     for (int t0 = 0; t0 < a.n_tiles; t0 += NT) {
@@ -261,12 +269,14 @@ __global__ __launch_bounds__(64 * kAdjWaves) void backproject_adjoint_kernel(con
             const int tx0 = (t % a.tiles_x) * 8, ty0 = (t / a.tiles_x) * 8;
             const double xa = a.x0 + tx0 * a.dx, xb = a.x0 + min(tx0 + 7, a.nx - 1) * a.dx;
             const double ya = a.y0 + ty0 * a.dy, yb = a.y0 + min(ty0 + 7, a.ny - 1) * a.dy;
-            const double lmin = rect_dist(xT, yT, xa, xb, ya, yb) + rect_dist(xR, yR, xa, xb, ya, yb);
+            double lmin = rect_dist(xT, yT, xa, xb, ya, yb);
+            lmin += a.mono ? lmin : rect_dist(xR, yR, xa, xb, ya, yb);
             double lmax = 0.0;
             for (int k = 0; k < 4; ++k) {
                 const double x = (k & 1) ? xb : xa, y = (k & 2) ? yb : ya;
-                lmax = fmax(lmax, sqrt((x - xT) * (x - xT) + (y - yT) * (y - yT)) +
-                                      sqrt((x - xR) * (x - xR) + (y - yR) * (y - yR)));
+                double l = sqrt((x - xT) * (x - xT) + (y - yT) * (y - yT));
+                l += a.mono ? l : sqrt((x - xR) * (x - xR) + (y - yR) * (y - yR));
+                lmax = fmax(lmax, l);
             }
             // taps floor(u) - 1 .. floor(u) + 2 reach [s0, s0 + S) only if
             // s0 - 2 <= u < s0 + S + 1
@@ -296,8 +306,8 @@ __global__ __launch_bounds__(64 * kAdjWaves) void backproject_adjoint_kernel(con
             float2 c0 = make_float2(0.f, 0.f), c1 = c0;
             if (px < a.nx && py < a.ny) {
                 const double xg = a.x0 + px * a.dx, yg = a.y0 + py * a.dy;
-                const double l = sqrt((xg - xT) * (xg - xT) + (yg - yT) * (yg - yT)) +
-                                 sqrt((xg - xR) * (xg - xR) + (yg - yR) * (yg - yR));
+                double l = sqrt((xg - xT) * (xg - xT) + (yg - yT) * (yg - yT));
+                l += a.mono ? l : sqrt((xg - xR) * (xg - xR) + (yg - yR) * (yg - yR));
                 const double u = (l - l0) * a.inv_du;
                 const double fl = floor(u);
                 const float tf = static_cast<float>(u - fl);
@@ -334,10 +344,11 @@ __global__ __launch_bounds__(64 * kAdjWaves) void backproject_adjoint_kernel(con
                 mypi[rank] = make_int2(pix, i0);
             }
             wave_lds_sync();   // the records, written by their lanes, read by every lane below
+            const int2 mine = mypi[lane];   // lane r: pixel and first tap of rank r (any value past n)
 
             // lane = k_z bin: walk the ranked pixels
             float2 a0 = make_float2(0.f, 0.f), a1 = a0, a2 = a0, a3 = a0;
-            int cur = __builtin_amdgcn_readfirstlane(mypi[0].y);
+            int cur = __builtin_amdgcn_readlane(mine.y, 0);
 #pragma unroll 1
             for (int q0 = 0; q0 < n; q0 += 8) {
                 // the next eight pixels' G~ first, so their latency is paid
@@ -347,13 +358,13 @@ __global__ __launch_bounds__(64 * kAdjWaves) void backproject_adjoint_kernel(con
                 adj_u32x2 gv[8];
 #pragma unroll
                 for (int qq = 0; qq < 8; ++qq) {
-                    const unsigned pix = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(mypi[q0 + qq].x));
+                    const unsigned pix = static_cast<unsigned>(__builtin_amdgcn_readlane(mine.x, q0 + qq));
                     gv[qq] = __builtin_amdgcn_raw_buffer_load_b64(grs, gvoff, pix * static_cast<unsigned>(a.n_z) * 8u, 0);
                 }
 #pragma unroll
                 for (int qq = 0; qq < 8; ++qq) {
                     if (q0 + qq >= n) break;  // wavefront-uniform
-                    const int pi0 = __builtin_amdgcn_readfirstlane(mypi[q0 + qq].y);
+                    const int pi0 = __builtin_amdgcn_readlane(mine.y, q0 + qq);
                     while (cur < pi0) {  // samples before this pixel's first tap are complete
                         if (cur >= 0 && cur < S) {
                             acr[cur] += a0.x;
@@ -460,6 +471,7 @@ int launch_backproject_adjoint(const HybridPlan& p, const DeviceTables& dt, cons
     a.n_tiles = a.tiles_x * ((p.ny + 7) / 8);
     a.n_seg = (p.n_l + kAdjSeg - 1) / kAdjSeg;
     a.block = p.block;
+    a.mono = p.mode == PL_MONO;
     const long long bins = (p.n_z + kAdjBins - 1) / kAdjBins;
     const long long work = static_cast<long long>(p.n_ch) * bins * a.n_seg;
     if (work > (1LL << 30)) return fail(PL_EUNSUPPORTED, "adjoint back-projection: too many work items");
