@@ -185,7 +185,7 @@ int launch_range_adjoint_wave(const HybridPlan& p, const float2* qt, char* ws, f
 // wavefront, of which 12 are the term's, 5 the window's moves, 10 the tile's
 // records and the tile list).  Ranks are read from lanes, not broadcast
 // through LDS, and a monostatic range takes one float64 root: 3.48 -> 3.20 ms
-// for the image of 256 x 128x128 voxels and 320 channels at 4 wavefronts per
+// for the image of 256 x 200x200 voxels and 320 channels at 4 wavefronts per
 // SIMD; at 3 (129 registers) 3.83.  Two bins per lane (half the records, 224
 // registers, 2 wavefronts) took 5.0 ms; accumulators kept by sample mod 4
 // instead of moved need selects that cost more than the moves.
