@@ -360,7 +360,10 @@ int hybrid_workspace_bytes(const pl_geometry* geom, const pl_image_grid* grid,
  * or wavefront count, run steps 2 and 3 on a coarser range grid of FP16 pairs
  * (22 bits) and on the matrix cores with FP32 accumulation, wherever the
  * planner finds that at a smaller interpolation error than the B-spline's;
- * mfma_backprojection = -1 asks for the vector kernels.
+ * mfma_backprojection = -1 asks for the vector kernels.  The BF16 and FP16
+ * modes with mfma_backprojection 0 or 1 do the same from 4096 pixels on (it
+ * is faster than their own kernels and more accurate); a requested tile,
+ * block or wavefront count keeps those.
  *   echo_dev   [n_channels][n_scan][n_freq] complex64, read only.
  *   image_dev  [n_scan][ny][nx] complex64 output; must not alias echo or ws.
  *   ws         device workspace of at least hybrid_workspace_bytes bytes,

@@ -234,7 +234,10 @@ double window_error(const std::vector<double>& X, double xm, const WindowWeights
 // image's error against float64 is 0.25 .. 0.85 of the B-spline path's over
 // 65 problems of 24 .. 509 scan positions and 2.2 .. 5.6 mm pixels; at 1.3 of
 // the B-spline's estimate it was 0.8 .. 1.9 of it.
-bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPlan& base, HybridPlan* out) {
+//
+// base: the call's plan in FP32; held: the plan that runs otherwise.
+bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPlan& base, const HybridPlan& held,
+                 HybridPlan* out) {
     if (base.precision != PL_PREC_FP32 || base.range_method != PL_RANGE_NUFFT || base.ref_mode != PL_REF_BAND_CENTRE ||
         base.interp != PL_INTERP_BSPLINE4 || base.sigma_l > 6.0 || base.force_tile || base.force_tile_y ||
         base.force_kpl || base.force_waves || base.force_kb || base.force_bp_mfma)
@@ -247,19 +250,24 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     p.n_blocks = (n_lo + kWindowBins - 1) / kWindowBins;
     std::vector<double> half(p.n_blocks, 0.0);
     p.half_band = 0.0;
-    for (int b = 0; b < p.n_blocks; ++b) {
-        // |k_z| of bins m and mirrors n - 1 - m (which is -(m + 1) steps)
-        const int m0 = b * kWindowBins, m1 = std::min(n_lo, m0 + kWindowBins) - 1;
-        const int top = m1 < p.n_z / 2 ? m1 + 1 : m1;
-        double lo = 1e300, hi = -1e300;
-        for (int m = m0; m <= top; ++m) {
+    // k_rho over the propagating frequencies of bins [m0, m1]; empty: hi < lo
+    auto band = [&](int m0, int m1, double* lo, double* hi) {
+        *lo = 1e300;
+        *hi = -1e300;
+        for (int m = m0; m <= m1; ++m) {
             const double kz = 2.0 * kPi * m / (p.n_z * g->scan_step), q = 0.25 * kz * kz;
             if (g->k[p.n_f - 1] * g->k[p.n_f - 1] <= q) continue;
             int f = 0;
             while (g->k[f] * g->k[f] <= q) ++f;
-            lo = std::min(lo, std::sqrt(g->k[f] * g->k[f] - q));
-            hi = std::max(hi, std::sqrt(g->k[p.n_f - 1] * g->k[p.n_f - 1] - q));
+            *lo = std::min(*lo, std::sqrt(g->k[f] * g->k[f] - q));
+            *hi = std::max(*hi, std::sqrt(g->k[p.n_f - 1] * g->k[p.n_f - 1] - q));
         }
+    };
+    for (int b = 0; b < p.n_blocks; ++b) {
+        // |k_z| of bins m and mirrors n - 1 - m (which is -(m + 1) steps)
+        const int m0 = b * kWindowBins, m1 = std::min(n_lo, m0 + kWindowBins) - 1;
+        double lo, hi;
+        band(m0, m1 < p.n_z / 2 ? m1 + 1 : m1, &lo, &hi);
         p.kref[b] = hi < lo ? 0.0 : 0.5 * (lo + hi);
         half[b] = hi < lo ? 0.0 : 0.5 * (hi - lo);
         p.half_band = std::max(p.half_band, half[b]);
@@ -268,19 +276,28 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     if (p.half_band * std::hypot(3.0 * grid->dx, 3.0 * grid->dy) * 2.0 / 5.66 > 1.1) return false;   // far over the bound
     // the B-spline's error, sqrt(2) (k' du / 2 pi)^4 at k': over all bands,
     // and over the lower half of |k_z|, where a scene's echo is strongest
+    auto spline_error = [](const std::vector<double>& h, size_t n, double du) {
+        double e2 = 0.0;
+        for (size_t b = 0; b < n; ++b) e2 += 2.0 * std::pow(h[b] * du / (2.0 * kPi), 8) / 9.0;
+        return std::sqrt(e2 / n);
+    };
     const int n_low = (p.n_blocks + 1) / 2;
-    double base_err = 0.0, base_low = 0.0;
-    for (int b = 0; b < p.n_blocks; ++b) {
-        const double e2 = 2.0 * std::pow(half[b] * base.du / (2.0 * kPi), 8) / 9.0;
-        base_err += e2;
-        if (b < n_low) base_low += e2;
-    }
-    base_err = std::sqrt(base_err / p.n_blocks);
-    base_low = std::sqrt(base_low / n_low);
+    const double base_err = spline_error(half, half.size(), base.du), base_low = spline_error(half, n_low, base.du);
     // Where the B-spline itself is off by about its largest estimate (2.3e-5,
     // a block as wide as the band of k', scans of up to some 70 positions) the
-    // two forms' images would differ by more than 2e-5: the vector kernels stay.
-    if (base_low > 1.6e-5 || base_err > 1.9e-5) return false;
+    // two forms' images would differ by more than 2e-5: the other plan stays.
+    // The matrix-core modes' own blocks are wider.
+    std::vector<double> own(half);
+    if (held.block != kWindowBins) {
+        own.clear();
+        for (int m0 = 0; m0 < n_lo; m0 += held.block) {
+            double lo, hi;
+            band(m0, std::min(m0 + held.block, p.n_z / 2), &lo, &hi);
+            own.push_back(hi < lo ? 0.0 : 0.5 * (hi - lo));
+        }
+    }
+    if (spline_error(own, (own.size() + 1) / 2, held.du) > 1.6e-5 || spline_error(own, own.size(), held.du) > 1.9e-5)
+        return false;
 
     const double gspan = std::hypot(3.0 * grid->dx, 3.0 * grid->dy) * 2.0;
     const double spans[5] = {3.4, 3.77, 4.25, 4.85, 5.66};
@@ -346,7 +363,7 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     const long long items = static_cast<long long>(p.tiles_x) * p.tiles_y * p.n_blocks;
     long long pieces = std::min<long long>(kMaxWindowPieces, items * ((p.n_ch + 1) / 2));
     const size_t scratch = static_cast<size_t>(PL_STATIC_SCRATCH_BYTES);
-    if (base.total <= scratch) {
+    if (held.total <= scratch) {
         if (p.total > scratch) return false;
         pieces = std::min<long long>(pieces, (scratch - p.total) / kWindowPieceBytes);
     }
@@ -705,8 +722,25 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
 
 int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* out) {
     if (int rc = make_plan(g, grid, opts, out)) return rc;
-    HybridPlan w;
-    if (window_plan(g, grid, *out, &w)) {
+    // The BF16 and FP16 modes with split operands (or the vector
+    // back-projection) take the window form of their FP32 plan: it is the
+    // more accurate and the faster one (256 k_z x 320 channels x 200x200
+    // pixels: 0.92 against 1.49 ms), from some 64x64 pixels on: at 44x44 its
+    // range compression costs what its back-projection gains (182 against
+    // 175 us; 48x77 and 68x87 even).
+    HybridPlan base = *out, w;
+    if (out->precision != PL_PREC_FP32) {
+        if ((out->force_bp_mfma != 0 && out->force_bp_mfma != 1) || out->nx * static_cast<long long>(out->ny) < 4096)
+            return PL_OK;
+        pl_hybrid_opts o = *opts;
+        o.precision = PL_PREC_FP32;
+        o.mfma_backprojection = 0;
+        if (make_plan(g, grid, &o, &base)) {
+            clear_error();
+            return PL_OK;
+        }
+    }
+    if (window_plan(g, grid, base, *out, &w)) {
         w.need = std::max(w.total, out->total);
         *out = w;
     }

@@ -115,3 +115,17 @@ def test_window_batch_is_the_single_calls():
     for i, out in enumerate(pr.reconstruct_hybrid_batch(batch, echoes)):
         single = pr.reconstruct_hybrid(geoms[i], CASES[names[i]][1], echoes[i], **opts[i])
         assert torch.equal(out, single), names[i]
+
+
+@pytest.mark.parametrize("precision,mbp", [("bf16", 1), ("fp16", 1), ("bf16", 0), ("fp16", 0)])
+@pytest.mark.parametrize("nx,ny,window", [(64, 64, True), (63, 65, False), (181, 131, True)])
+def test_split_modes_take_the_window_form(precision, mbp, nx, ny, window):
+    # from 4096 pixels on the modes run their FP32 plan's window form
+    a, g = replace(MONO, n_elem=5, n_scan=224), grid(nx, ny, 0.0024)
+    geom = pr.make_geometry(a)
+    echo = dev(W.random_echo(a, 4))
+    got = pr.reconstruct_hybrid(geom, g, echo, precision=precision, mfma_backprojection=mbp)
+    assert torch.equal(got, pr.reconstruct_hybrid(geom, g, echo)) == window
+    if not mbp:   # an asked-for kernel keeps the mode's own plan
+        own = pr.reconstruct_hybrid(geom, g, echo, precision=precision, mfma_backprojection=-1)
+        assert torch.equal(got, own) != window and rel(host(got), host(own)) < TOL
