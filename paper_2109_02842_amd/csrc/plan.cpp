@@ -257,9 +257,9 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
         for (int m = m0; m <= m1; ++m) {
             const double kz = 2.0 * kPi * m / (p.n_z * g->scan_step), q = 0.25 * kz * kz;
             if (g->k[p.n_f - 1] * g->k[p.n_f - 1] <= q) continue;
-            int f = 0;
-            while (g->k[f] * g->k[f] <= q) ++f;
-            *lo = std::min(*lo, std::sqrt(g->k[f] * g->k[f] - q));
+            // the first propagating frequency (k rises with f)
+            const double kf = *std::partition_point(g->k.begin(), g->k.end(), [&](double k) { return k * k <= q; });
+            *lo = std::min(*lo, std::sqrt(kf * kf - q));
             *hi = std::max(*hi, std::sqrt(g->k[p.n_f - 1] * g->k[p.n_f - 1] - q));
         }
     };
@@ -302,24 +302,33 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     const double gspan = std::hypot(3.0 * grid->dx, 3.0 * grid->dy) * 2.0;
     const double spans[5] = {3.4, 3.77, 4.25, 4.85, 5.66};
     WindowWeights w;
+    auto admitted = [&](int step, int i) {
+        p.win_step = step;
+        p.win_span = spans[i];
+        p.du = gspan / spans[i];
+        p.sigma_used = kPi / (p.half_band * p.du);
+        if (p.sigma_used < 1.3) return false;
+        std::vector<double> X;
+        for (double h : half) X.push_back(h * p.du);
+        // positions: half the span, half a step of the window's start, and
+        // 1/64 sample and float rounding of the group's lowest position
+        const double xm = 0.5 * (spans[i] + step) + 0.02;
+        p.win_z = 2.0 / (xm * xm);
+        window_design(X, xm, &w);
+        return window_error(X, xm, w) <= (step == 2 ? 0.55 : 0.9) * base_err &&
+               window_error({X.begin(), X.begin() + n_low}, xm, w) <= 1.5 * base_low;
+    };
     bool found = false;
-    for (int step = 2; step >= 1 && !found; --step)
-        for (int i = 0; i < 5 && !found; ++i) {
-            p.win_step = step;
-            p.win_span = spans[i];
-            p.du = gspan / spans[i];
-            p.sigma_used = kPi / (p.half_band * p.du);
-            if (p.sigma_used < 1.3) continue;
-            std::vector<double> X;
-            for (double h : half) X.push_back(h * p.du);
-            // positions: half the span, half a step of the window's start, and
-            // 1/64 sample and float rounding of the group's lowest position
-            const double xm = 0.5 * (spans[i] + step) + 0.02;
-            p.win_z = 2.0 / (xm * xm);
-            window_design(X, xm, &w);
-            found = window_error(X, xm, w) <= (step == 2 ? 0.55 : 0.9) * base_err &&
-                    window_error({X.begin(), X.begin() + n_low}, xm, w) <= 1.5 * base_low;
+    for (int step = 2; step >= 1 && !found; --step) {
+        if (!admitted(step, 4)) continue;   // the narrowest step
+        int lo = 0, hi = 4;                 // the error falls with the step: the first of the five admitted
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (admitted(step, mid)) hi = mid;
+            else lo = mid + 1;
         }
+        found = admitted(step, hi);
+    }
     if (!found) return false;
     for (int k = 0; k < kWindowDegree; ++k)
         for (int s = 0; s < 4; ++s) {
