@@ -31,11 +31,13 @@ FLOP_PER_TERM = 24                  # (8 + 4P) with P = 4 interpolation taps
 CPU_SHARE_THREADS = 16              # host threads that come with one GPU
 
 
-def stage_rooflines(plan, a, wl, geom, stage, args):
+def stage_rooflines(plan, a, wl, geom, stage, args, window=False):
     """Algorithmic HBM bytes (and, for the FP32 NUFFT, FLOP) of the other
     stages over their event-timed durations: the FFTs move the cube in and
     out once; range compression reads the spectrum and writes the profiles
-    (FLOP per (c, k_z) pair: 5 n log2 n + n_f W 14 + 2 n_l with n = n_fine)."""
+    (FLOP per (c, k_z) pair: 5 n log2 n + n_f W 14 + 2 n_l with n = n_fine).
+    A call of the matrix-core window form has its own, coarser range grid,
+    whose sizes the plan does not report: no range compression entry then."""
     n_pairs = geom.n_channels * a.n_scan
     npix = wl.grid.nx * wl.grid.ny
     out = {}
@@ -47,8 +49,10 @@ def stage_rooflines(plan, a, wl, geom, stage, args):
                      "frac": gbs / HBM_PEAK_GBS}
 
     hbm("scan_fft", 2 * n_pairs * a.n_freq * 8)
-    hbm("range_compress", n_pairs * (a.n_freq + plan.n_l) * 8)
     hbm("kz_ifft", 2 * npix * a.n_scan * 8)
+    if window:
+        return out
+    hbm("range_compress", n_pairs * (a.n_freq + plan.n_l) * 8)
     if args.precision == "fp32" and args.range_method == "nufft":
         n = plan.n_fine
         flop = n_pairs * (5 * n * math.log2(n) + a.n_freq * plan.kernel_width * 14 + 2 * plan.n_l)
@@ -58,13 +62,33 @@ def stage_rooflines(plan, a, wl, geom, stage, args):
     return out
 
 
-def bp_roofline(plan, terms: int, bp_ms: float) -> dict:
+def takes_window(pr, torch, geom, grid, echo, opts) -> bool:
+    """Whether a whole call with these options runs the matrix-core window
+    form of the FP32 plan: its image is the FP32 call's bit for bit, and
+    differs in the last digits from that of the vector kernels, which
+    mfma_backprojection=-1 asks for."""
+    if opts.get("mfma_backprojection", 0) not in (0, 1):
+        return False
+    fp32 = dict(opts, precision="fp32", mfma_backprojection=0)
+    img = pr.reconstruct_hybrid(geom, grid, echo, **fp32)
+    if torch.equal(img, pr.reconstruct_hybrid(geom, grid, echo, **dict(fp32, mfma_backprojection=-1))):
+        return False
+    return opts.get("precision", "fp32") == "fp32" or torch.equal(img, pr.reconstruct_hybrid(geom, grid, echo, **opts))
+
+
+def bp_roofline(plan, terms: int, bp_ms: float, window=False) -> dict:
     """The back-projection's algorithmic FLOP rate over its event-timed
     launch against the roof of the unit it runs on: the FP32 vector peak for
     the VALU kernels, the dense BF16 / FP16 matrix-core peak for the MFMA
     kernels (which issue 6 (split) or 2 (single pass) MFMA 16x16x32 per
-    (4x4 pixels, 16 k_z, channel); that rate is reported as issued_tflops)."""
+    (4x4 pixels, 16 k_z, channel); that rate is reported as issued_tflops).
+    The window form of the FP32 path issues three 32x32x16 products per
+    (4x4 pixels, 32 k_z, channel)."""
     achieved = FLOP_PER_TERM * terms / (bp_ms * 1e-3) / 1e12
+    if window:
+        return {"bound": "mfma", "achieved": achieved, "peak": BF16_MFMA_PEAK_TFLOPS,
+                "frac": achieved / BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
+                "issued_tflops": 3 * 2 * 32 * 32 * 16 / 512 * terms / (bp_ms * 1e-3) / 1e12}
     if plan.mfma_backprojection:
         n_mfma = 2 if plan.bp_kernel == "mfma-1pass" else 6
         return {"bound": "mfma", "achieved": achieved, "peak": BF16_MFMA_PEAK_TFLOPS,
@@ -316,10 +340,11 @@ def bench_c3(args, torch, pr, W):
     # the GPU timings first, the host-side checks after (see main)
     for name, opts in paths:
         ms, stage, _, med, plan = time_path(opts, steps, 2, min_warm_s=0.3)
+        win = takes_window(pr, torch, geom, wl.grid, echo, opts)
         res[name] = {"value": voxels / (ms * 1e-3), "unit": "voxels/s", "ms_per_step": ms, "median_ms": med,
-                     "steps": steps, "stages_ms": stage, "bp_kernel": plan.bp_kernel,
+                     "steps": steps, "stages_ms": stage, "bp_kernel": "window" if win else plan.bp_kernel,
                      "roofline": bp_roofline(plan, a.n_scan * wl.grid.nx * wl.grid.ny * geom.n_channels,
-                                             stage["backproject"])}
+                                             stage["backproject"], win)}
         log(f"[bench] C3 {name}: {ms:.3f} ms/step ({voxels / (ms * 1e-3):.3e} voxels/s)")
     if not args.no_variants:
         ams = time_adjoint(pr, torch, geom, wl.grid, img, steps, 2)
@@ -440,7 +465,8 @@ def main() -> int:
     value = voxels / (ms * 1e-3)
     terms = a.n_scan * wl.grid.nx * wl.grid.ny * geom.n_channels
     bp_ms = stage["backproject"]
-    roof = bp_roofline(plan, terms, bp_ms)
+    window = takes_window(pr, torch, geom, wl.grid, echo, opts)
+    roof = bp_roofline(plan, terms, bp_ms, window)
     out = {
         "metric": METRIC, "value": value, "unit": "voxels/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
@@ -451,10 +477,10 @@ def main() -> int:
                    "interp": args.interp, "l_oversample": args.l_oversample, "nufft_tol": 1e-6,
                    "tile": list(plan.tile), "kz_block": plan.block},
         "roofline": dict(roof,
-                         traffic=measured_traffic(plan.bp_kernel, args.config, args.precision, plan.n_l),
+                         traffic=measured_traffic("window" if window else plan.bp_kernel, args.config, args.precision, plan.n_l),
                          kernel="backproject", flop_per_launch=FLOP_PER_TERM * terms, avg_launch_ms=bp_ms),
         "stages_ms": stage,
-        "stages_roofline": stage_rooflines(plan, a, wl, geom, stage, args),
+        "stages_roofline": stage_rooflines(plan, a, wl, geom, stage, args, window),
         "plan_build_ms": first_ms,
     }
     # Every GPU timing of this workload first, then the checks against the
@@ -464,7 +490,7 @@ def main() -> int:
     if not args.no_variants:
         out["variants"] = {}
         for name, prec, mbp, rm in (("bf16", "bf16", 0, "nufft"), ("fp16", "fp16", 0, "nufft"),
-                                    ("fp32", "fp32", 0, "nufft"), ("bf16-mfma-bp", "bf16", 1, "nufft"),
+                                    ("fp32", "fp32", 0, "nufft"), ("fp32-vector-bp", "fp32", -1, "nufft"), ("bf16-mfma-bp", "bf16", 1, "nufft"),
                                     ("fp16-mfma-bp", "fp16", 1, "nufft"), ("fp16-mfma-bp-1pass", "fp16", 2, "nufft"),
                                     ("fp32-resample", "fp32", 0, "resample")):
             if prec == args.precision and mbp == args.mfma_bp and rm == args.range_method:
@@ -473,9 +499,10 @@ def main() -> int:
             if mbp:
                 vopts.update(tile=0, tile_y=0, kz_block=0, kz_per_lane=0, waves=0)
             vms, vstage, _, vmed, vplan = time_path(vopts, args.steps, args.warmup)
+            vwin = takes_window(pr, torch, geom, wl.grid, echo, vopts)
             out["variants"][name] = {"value": voxels / (vms * 1e-3), "ms_per_step": vms, "stages_ms": vstage,
-                                     "speedup_vs_main": ms / vms, "bp_kernel": vplan.bp_kernel,
-                                     "roofline": bp_roofline(vplan, terms, vstage["backproject"])}
+                                     "speedup_vs_main": ms / vms, "bp_kernel": "window" if vwin else vplan.bp_kernel,
+                                     "roofline": bp_roofline(vplan, terms, vstage["backproject"], vwin)}
             vopts_of[name] = vopts
             log(f"[bench] {name}: {vms:.3f} ms/step; range_compress {vstage['range_compress']:.3f} ms; "
                 f"backproject {vstage['backproject']:.3f} ms")
