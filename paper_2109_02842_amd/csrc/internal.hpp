@@ -36,7 +36,7 @@ constexpr int kWindowDegree = 5;
 constexpr int kSpectrumMaxParts = 256;
 constexpr int kMaxWindowPieces = 512;      // partial spectra of split items (16x16 pixels x 64 rows)
 constexpr size_t kWindowPieceBytes = 16ull * 16 * 2 * kWindowBins * 8;
-constexpr int kMaxGL = 64;          // quadrature nodes for the kernel transform
+constexpr int kMaxGL = 32;          // positive quadrature nodes for the kernel transform
 constexpr int kMaxRadices = 16;
 
 // ---------------------------------------------------------------- errors

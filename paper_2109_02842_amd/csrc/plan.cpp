@@ -12,9 +12,10 @@ namespace {
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
-// Gauss-Legendre nodes and weights on [-1, 1] (Newton iteration on P_n).
+// The n / 2 positive Gauss-Legendre nodes on [-1, 1] and their weights, n
+// even (Newton iteration on P_n).
 void gauss_legendre(int n, double* x, double* w) {
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i < n / 2; ++i) {
         double z = std::cos(kPi * (i + 0.75) / (n + 0.5));
         double dp = 1.0;
         for (int it = 0; it < 100; ++it) {
@@ -63,8 +64,12 @@ int set_spreading(HybridPlan* plan, double sigma) {
     }
     p.h = 0.5 * p.W;
     if (p.n_fine / sigma + 2 * p.W + 2 >= p.n_fine) return fail(PL_EUNSUPPORTED, "fine grid too short");
-    p.n_gl = std::min(kMaxGL, 4 * p.W + 16);
-    gauss_legendre(p.n_gl, p.gl_x, p.gl_w);
+    // quadrature of the kernel's transform: an even integrand, so the positive
+    // nodes of an even rule, their weights doubled and times the kernel
+    p.n_gl = std::min(2 * kMaxGL, 4 * p.W + 16) / 2;
+    gauss_legendre(2 * p.n_gl, p.gl_x, p.gl_w);
+    for (int q = 0; q < p.n_gl; ++q)
+        p.gl_w[q] *= 2.0 * std::exp(p.beta * (std::sqrt(1.0 - p.gl_x[q] * p.gl_x[q]) - 1.0));
     return PL_OK;
 }
 
