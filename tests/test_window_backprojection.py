@@ -62,9 +62,9 @@ MULTI = W.ArrayDesc(mode="multi", n_chords=3, radius=0.5, n_elem=11, spacing=W._
 CASES = {
     "mono-fine": (MONO, grid(45, 29, 0.0026)),
     "mono-coarse": (MONO, grid(45, 29, 0.0046)),
-    "mono-1x1": (MONO, grid(1, 1, 0.003)),
-    "mono-331": (replace(MONO, n_scan=331), grid(17, 33, 0.003)),
-    "multi-fine": (MULTI, grid(27, 35, 0.0024)),
+    "mono-one-tile": (MONO, grid(13, 15, 0.003)),
+    "mono-331": (replace(MONO, n_scan=331), grid(30, 48, 0.003)),
+    "multi-fine": (MULTI, grid(27, 47, 0.0024)),
     "multi-coarse": (MULTI, grid(15, 50, 0.0038)),
 }
 
@@ -110,7 +110,7 @@ def test_window_batch_is_the_single_calls():
     geoms = [pr.make_geometry(CASES[n][0]) for n in names]
     echoes = [dev(W.random_echo(CASES[n][0], 70 + i)) for i, n in enumerate(names)]
     # one scan with an asked-for kernel: both queues in one call
-    opts = [{} if n != "mono-1x1" else dict(mfma_backprojection=-1) for n in names]
+    opts = [{} if n != "mono-one-tile" else dict(mfma_backprojection=-1) for n in names]
     batch = pr.HybridBatch(geoms, [CASES[n][1] for n in names], opts)
     for i, out in enumerate(pr.reconstruct_hybrid_batch(batch, echoes)):
         single = pr.reconstruct_hybrid(geoms[i], CASES[names[i]][1], echoes[i], **opts[i])
