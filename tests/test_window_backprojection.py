@@ -65,7 +65,7 @@ CASES = {
     "mono-one-tile": (MONO, grid(13, 15, 0.003)),
     "mono-331": (replace(MONO, n_scan=331), grid(30, 48, 0.003)),
     "multi-fine": (MULTI, grid(27, 47, 0.0024)),
-    "multi-coarse": (MULTI, grid(15, 50, 0.0038)),
+    "multi-coarse": (MULTI, grid(15, 62, 0.0038)),
 }
 
 
