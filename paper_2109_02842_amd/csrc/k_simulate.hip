@@ -6,13 +6,18 @@
 namespace pl {
 namespace {
 
-// sqrt(x) for x >= 0 to double precision: hardware FP32 root (about 1 ulp),
-// then one Newton step whose residual is formed in FP64.
-__device__ __forceinline__ double sqrt_dp(double x) {
-    const float r = __builtin_amdgcn_sqrtf(static_cast<float>(x));
-    const double rd = r;
-    const float corr = static_cast<float>(x - rd * rd) * (0.5f * __builtin_amdgcn_rcpf(r));
-    return r > 0.f ? rd + static_cast<double>(corr) : 0.0;
+// sqrt(x) to float64 accuracy (1 ulp) without the library root's scaling of
+// tiny and huge arguments: the hardware reciprocal root (2^-24), one coupled
+// Goldschmidt step for root and half reciprocal (2^-47), one Newton step.
+// x = 0 and x that is not a number are returned, infinity is not a number.
+__device__ __forceinline__ double path_root(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : x;
 }
 
 constexpr int kSimRun = 32;   // scatterers summed before they join the total
@@ -32,7 +37,8 @@ struct SimArgs {
 // Runs of 32 scatterers are summed apart, which keeps the rounding of long
 // sums down (4e-7 of the cube at 2000 scatterers; 1.2e-6 in one sum).  Bound
 // by VALU issue: 320 channels x 256 positions x 64 frequencies of 2000
-// scatterers take 1.96 ms (2.55 with the advanced phasor, whose error was 1e-6).
+// scatterers take 1.92 ms (2.55 with the advanced phasor, whose error was
+// 1e-6; 2.09 with the library's root).
 template <int A, bool MONO>
 __global__ __launch_bounds__(256) void simulate_kernel(const double* __restrict__ chan,
                                                        const double* __restrict__ k,
@@ -68,8 +74,8 @@ __global__ __launch_bounds__(256) void simulate_kernel(const double* __restrict_
             const double px = xyz[3 * s], py = xyz[3 * s + 1], pz = xyz[3 * s + 2];
             const float2 sig = make_float2(static_cast<float>(refl[2 * s]), static_cast<float>(refl[2 * s + 1]));
             const double dzp = pz - zm, dz2 = dzp * dzp;
-            double d = sqrt_dp((px - xt) * (px - xt) + (py - yt) * (py - yt) + dz2);
-            d += MONO ? d : sqrt_dp((px - xr) * (px - xr) + (py - yr) * (py - yr) + dz2);
+            double d = path_root((px - xt) * (px - xt) + (py - yt) * (py - yt) + dz2);
+            d += MONO ? d : path_root((px - xr) * (px - xr) + (py - yr) * (py - yr) + dz2);
             float2 w[8], u = cmul(sig, cis_rev(-k0_rev * d));
             const float2 st8 = cis_rev(-8.0 * dk_rev * d);
             w[1] = cis_rev(-dk_rev * d);
@@ -106,6 +112,15 @@ __global__ void weight_echo_kernel(const float2* __restrict__ echo, const double
     const long long i = blockIdx.x * 256LL + threadIdx.x;
     if (i >= total) return;
     out[i] = cscale(echo[i], static_cast<float>(k[i % n_f]));
+}
+
+// sqrt(x) for x >= 0 to double precision: hardware FP32 root (about 1 ulp),
+// then one Newton step whose residual is formed in FP64.
+__device__ __forceinline__ double sqrt_dp(double x) {
+    const float r = __builtin_amdgcn_sqrtf(static_cast<float>(x));
+    const double rd = r;
+    const float corr = static_cast<float>(x - rd * rd) * (0.5f * __builtin_amdgcn_rcpf(r));
+    return r > 0.f ? rd + static_cast<double>(corr) : 0.0;
 }
 
 struct BpArgs {
