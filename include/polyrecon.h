@@ -358,9 +358,10 @@ int hybrid_workspace_bytes(const pl_geometry* geom, const pl_image_grid* grid,
  * to the tolerance the options set.  FP32 plans with the default range method,
  * interpolation and references, and without a requested tile, block, kernel
  * or wavefront count, run steps 2 and 3 on a coarser range grid of FP16 pairs
- * (22 bits) and on the matrix cores with FP32 accumulation, wherever the
- * planner finds that at a smaller interpolation error than the B-spline's;
- * mfma_backprojection = -1 asks for the vector kernels.  The BF16 and FP16
+ * (22 bits) and on the matrix cores with FP32 accumulation, where the planner
+ * estimates an interpolation error below the B-spline's over all k_z (at most
+ * 1.05 of it over every range of |k_z| from 0 up); mfma_backprojection = -1
+ * asks for the vector kernels.  The BF16 and FP16
  * modes with mfma_backprojection 0 or 1 do the same from 4096 pixels on (it
  * is faster than their own kernels and more accurate); a requested tile,
  * block or wavefront count keeps those.

@@ -116,25 +116,27 @@ int set_layout(HybridPlan* plan) {
 
 // Weights of the window back-projection: the least-squares interpolator of
 // e^{j th x} from the eight samples at s - 3.5, for positions |x| <= xm and
-// th spread evenly over each block's band [-X_b, X_b] (X_b = half band x du).
-// Its normal matrix and right-hand side are means of sinc(X_b (s - s')) and
-// sinc(X_b (x - s)); the symmetry w_{7-s}(x) = w_s(-x) splits them into 4 x 4
-// systems for the even and odd parts, which are solved at kWindowDegree
-// Chebyshev nodes of x^2 and fitted by polynomials in z = 2 x^2 / xm^2 - 1
-// (w = E + x O; in z their terms stay near the size of the weights, while
-// powers of x^2 cancel and would cost two digits in float32).
-// Returns the rms error over x and th, polynomials included.
+// th spread evenly over each block's band [-X_b, X_b] (X_b = half band x du),
+// block b's squared error counted share_b times.  Its normal matrix and
+// right-hand side are means of sinc(X_b (s - s')) and sinc(X_b (x - s)); the
+// symmetry w_{7-s}(x) = w_s(-x) splits them into 4 x 4 systems for the even
+// and odd parts, which are solved at kWindowDegree Chebyshev nodes of x^2 and
+// fitted by polynomials in z = 2 x^2 / xm^2 - 1 (w = E + x O; in z their terms
+// stay near the size of the weights, while powers of x^2 cancel and would cost
+// two digits in float32).
 struct WindowWeights {
     double even[kWindowDegree][4], odd[kWindowDegree][4];
 };
 
-double mean_sinc(const std::vector<double>& X, double x) {
-    double s = 0.0;
-    for (double b : X) {
-        const double y = b * x;
-        s += std::fabs(y) < 1e-6 ? 1.0 - y * y / 6.0 : std::sin(y) / y;
+// mean over the blocks by their shares (none: equal ones)
+double mean_sinc(const std::vector<double>& X, const std::vector<double>& share, double x) {
+    double s = 0.0, n = 0.0;
+    for (size_t b = 0; b < X.size(); ++b) {
+        const double y = X[b] * x, f = share.empty() ? 1.0 : share[b];
+        s += f * (std::fabs(y) < 1e-6 ? 1.0 - y * y / 6.0 : std::sin(y) / y);
+        n += f;
     }
-    return s / static_cast<double>(X.size());
+    return s / n;
 }
 
 // b = A^-1 b by elimination with row exchanges
@@ -158,17 +160,17 @@ void solve(double (&A)[N][N], double (&b)[N]) {
     }
 }
 
-void window_design(const std::vector<double>& X, double xm, WindowWeights* out) {
+void window_design(const std::vector<double>& X, const std::vector<double>& share, double xm, WindowWeights* out) {
     constexpr int D = kWindowDegree;
     double g[8];   // mean sinc at whole sample distances
-    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, d);
+    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, share, d);
     const double ym = xm * xm;
     double node[D], E[D][4], O[D][4];
     for (int i = 0; i < D; ++i) {
         node[i] = std::cos(kPi * (i + 0.5) / D);
         const double x = std::sqrt(0.5 * (1.0 + node[i]) * ym);
         double b[8];
-        for (int s = 0; s < 8; ++s) b[s] = mean_sinc(X, x - (s - 3.5));
+        for (int s = 0; s < 8; ++s) b[s] = mean_sinc(X, share, x - (s - 3.5));
         for (int par = 0; par < 2; ++par) {
             const double sg = par ? -1.0 : 1.0;
             double A[4][4], r[4];
@@ -200,7 +202,7 @@ double window_error(const std::vector<double>& X, double xm, const WindowWeights
     constexpr int D = kWindowDegree;
     const double ym = xm * xm;
     double g[8];
-    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, d);
+    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, {}, d);
     double err = 0.0;
     constexpr int NX = 9;
     for (int i = 0; i < NX; ++i) {
@@ -216,12 +218,45 @@ double window_error(const std::vector<double>& X, double xm, const WindowWeights
             w[7 - s] = ev - x * od;
         }
         for (int s = 0; s < 8; ++s) {
-            e -= 2.0 * w[s] * mean_sinc(X, x - (s - 3.5));
+            e -= 2.0 * w[s] * mean_sinc(X, {}, x - (s - 3.5));
             for (int t = 0; t < 8; ++t) e += w[s] * w[t] * g[std::abs(s - t)];
         }
         err += std::max(e, 0.0);
     }
     return std::sqrt(err / NX);
+}
+
+// Squared error of these weights at n phase steps per sample th[i], mean over
+// the positions |x| <= xm, polynomials included.
+void window_error(const double* th, int n, double xm, const WindowWeights& wt, double* e2) {
+    constexpr int D = kWindowDegree, NX = 9;
+    for (int i = 0; i < n; ++i) e2[i] = 0.0;
+    for (int j = 0; j < NX; ++j) {
+        const double x = xm * (j + 0.5) / NX, z = 2.0 * x * x / (xm * xm) - 1.0;
+        double w[8];
+        for (int s = 0; s < 4; ++s) {
+            double ev = 0.0, od = 0.0;
+            for (int k = D - 1; k >= 0; --k) {
+                ev = ev * z + wt.even[k][s];
+                od = od * z + wt.odd[k][s];
+            }
+            w[s] = ev + x * od;
+            w[7 - s] = ev - x * od;
+        }
+        for (int i = 0; i < n; ++i) {
+            // sum_s w_s e^{j th (s - 3.5 - x)} - 1 by the powers of e^{j th}
+            const double cs = std::cos(th[i]), sn = std::sin(th[i]);
+            double re = 0.0, im = 0.0;
+            for (int s = 7; s >= 0; --s) {
+                const double t = re * cs - im * sn + w[s];
+                im = re * sn + im * cs;
+                re = t;
+            }
+            const double ph = th[i] * (x + 3.5), c0 = std::cos(ph), s0 = std::sin(ph);
+            const double dr = re * c0 + im * s0 - 1.0, di = im * c0 - re * s0;
+            e2[i] += (dr * dr + di * di) / NX;
+        }
+    }
 }
 
 // The window plan of a whole FP32 call (see k_backproject_window.hip), or
@@ -232,13 +267,25 @@ double window_error(const std::vector<double>& X, double xm, const WindowWeights
 //
 // The range step: a group's ranges span at most gspan = 2 |(3 dx, 3 dy)|
 // (|grad l| <= 2); the step is the widest of five (gspan = 3.4 .. 5.66
-// samples) whose estimated interpolation error is smaller than the B-spline's
-// at the caller's oversampling over the same bands: 0.55 of it with even
-// window starts, 0.9 with any start, and 1.5 over the lower half of |k_z|
-// (the B-spline's falls faster towards a band's centre).  At those lines the
-// image's error against float64 is 0.25 .. 0.85 of the B-spline path's over
-// 65 problems of 24 .. 509 scan positions and 2.2 .. 5.6 mm pixels; at 1.3 of
-// the B-spline's estimate it was 0.8 .. 1.9 of it.
+// samples) at which equal shares of all blocks give an estimated interpolation
+// error of 0.55 of the B-spline's at the caller's oversampling over the same
+// bands (even window starts) or 0.9 of it (any start), and at most 1.5 of it
+// over the lower half of |k_z|.
+//
+// The shares: the B-spline's error falls as the fourth power of a block's
+// band, these weights' hardly, and an echo's energy lies at the |k_z| its
+// aperture sees, from 0 up: with equal shares the image was less exact than
+// the B-spline path's where the lowest blocks are much narrower than the rest
+// (10 of 278 problems of 72 .. 512 scan positions and 2.2 .. 5.6 mm pixels, by
+// up to 2.06, all but two of them with a 3 mm scan step; an echo at k_z = 0
+// alone by up to 3.7).  Shares h_b^(-8 gamma) (h_b the block's half band) trade
+// error of the wide bands for the narrow ones'.  For each gamma both forms'
+// squared errors are summed over the k' of every propagating (frequency, bin),
+// in the blocks each form has, from k_z = 0 up to six fractions of |k_z|; the
+// first gamma at which the largest of the six ratios is below 0.9 is taken, or
+// the one where it is smallest, which has to be at most 1.05 (9 of the 278 keep
+// the other plan).  The 269 have 0.35 of the B-spline path's error in the mean,
+// two of them more than it (1.5e-6 against 1.2e-6, 2.0e-6 against 1.5e-6).
 //
 // base: the call's plan in FP32; held: the plan that runs otherwise.
 bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPlan& base, const HybridPlan& held,
@@ -325,7 +372,7 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
         // 1/64 sample and float rounding of the group's lowest position
         const double xm = 0.5 * (spans[i] + step) + 0.02;
         p.win_z = 2.0 / (xm * xm);
-        window_design(X, xm, &w);
+        window_design(X, {}, xm, &w);
         return window_error(X, xm, w) <= (step == 2 ? 0.55 : 0.9) * base_err &&
                window_error({X.begin(), X.begin() + n_low}, xm, w) <= 1.5 * base_low;
     };
@@ -341,6 +388,55 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
         found = admitted(step, hi);
     }
     if (!found) return false;
+
+    // the shares (see above)
+    constexpr double kBelow = 0.9, kMost = 1.05;
+    constexpr int kPhase = 48;   // cells of |k'|
+    const double fraction[6] = {0.125, 0.25, 0.375, 0.5, 0.75, 1.0};
+    double count[6][kPhase] = {}, spline[6] = {}, th[kPhase], e2[kPhase];
+    for (int i = 0; i < kPhase; ++i) th[i] = (i + 0.5) / kPhase * p.half_band * p.du;
+    const int last = p.n_z / 2;   // bins m = 0 .. last and -m
+    const int fs = std::max(1, p.n_f / 8);
+    for (int m = 0; m <= last; ++m) {
+        const double kz = 2.0 * kPi * m / (p.n_z * g->scan_step), q = 0.25 * kz * kz;
+        int part = 0;
+        while (part < 5 && m > fraction[part] * last) ++part;
+        for (int f = 0; f < p.n_f; f += fs) {
+            if (g->k[f] * g->k[f] <= q) continue;
+            const double kr = std::sqrt(g->k[f] * g->k[f] - q);
+            for (int sg = 0; sg < 2; ++sg) {
+                const int kap = sg && m ? p.n_z - m : m;
+                const double kw = std::fabs(kr - p.kref[std::min(kap, p.n_z - 1 - kap) / kWindowBins]);
+                const double x = (kr - base.kref[kap / base.block]) * base.du / (2.0 * kPi);
+                ++count[part][std::min(kPhase - 1, static_cast<int>(kw / p.half_band * kPhase))];
+                spline[part] += 2.0 * (x * x * x * x) * (x * x * x * x);
+            }
+        }
+    }
+    std::vector<double> X;
+    for (double h : half) X.push_back(h * p.du);
+    const double xm = 0.5 * (p.win_span + p.win_step) + 0.02;
+    double least = 1e300;
+    for (double gamma : {0.0, 0.5, 0.75, 1.0, 1.25, 1.5, 1.75, 2.0, 2.5}) {
+        std::vector<double> share;
+        for (double h : half) share.push_back(std::pow(std::max(h / p.half_band, 0.25), -8.0 * gamma));
+        WindowWeights t;
+        window_design(X, share, xm, &t);
+        window_error(th, kPhase, xm, t, e2);
+        double worst = 0.0, sw = 0.0, ss = 0.0;
+        for (int i = 0; i < 6; ++i) {
+            for (int j = 0; j < kPhase; ++j) sw += count[i][j] * e2[j];
+            ss += spline[i];
+            const double r = std::sqrt(sw / ss);
+            if (!(r <= worst)) worst = r;   // also one that is not a number
+        }
+        if (worst < least) {
+            least = worst;
+            w = t;
+        }
+        if (least <= kBelow) break;
+    }
+    if (!(least <= kMost)) return false;
     for (int k = 0; k < kWindowDegree; ++k)
         for (int s = 0; s < 4; ++s) {
             p.win_even[k][s] = static_cast<float>(w.even[k][s]);
