@@ -277,7 +277,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // FP16 hi + lo profiles): m = the largest spectrum part (in
 // kSpectrumMaxParts parts), |q| < m 2^log2_gain.  One g for the call: FP16
 // pairs keep 22 bits down to 2^-17 of the bound and an absolute 2^-39 of it
-// below.  Wavefront-uniform.
+// below.  From about -135 (echoes of subnormal floats) to 140.
+// Wavefront-uniform.
 __device__ __forceinline__ int profile_exponent(const float* __restrict__ parts, int log2_gain, int lane) {
     static_assert(kSpectrumMaxParts % 64 == 0, "whole wavefront reads");
     float m = 0.f;
@@ -285,7 +286,7 @@ __device__ __forceinline__ int profile_exponent(const float* __restrict__ parts,
     for (int i = 0; i < kSpectrumMaxParts; i += 64) m = fmaxf(m, parts[i + lane]);
     for (int d = 32; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
     const int e = static_cast<int>((__float_as_uint(m) >> 23) & 255u) - 127;
-    return __builtin_amdgcn_readfirstlane(m > 0.f ? max(e + 1 + log2_gain - 15, -100) : 0);
+    return __builtin_amdgcn_readfirstlane(m > 0.f ? e + 1 + log2_gain - 15 : 0);
 }
 
 constexpr int kWaveRow = 72;   // complex values per row of the transposed stages

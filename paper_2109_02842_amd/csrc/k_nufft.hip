@@ -253,7 +253,9 @@ __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict
     const double lmid = llo[c] + (a.n_l / 2) * a.du;
     const double cell = a.du * N * (0.5 / kPi);
 
-    const int g = HILO ? profile_exponent(a.smax, a.log2_gain, lane) : 0;
+    // 2^-g in two factors, one for the weights and one for the spectrum: the
+    // smallest echoes take it past the float range of the weights
+    const int g = HILO ? profile_exponent(a.smax, a.log2_gain, lane) : 0, gw = max(g, -100);
     // strengths and positions; first propagating frequency by ballot
     int f0 = a.n_f;
     for (int fb = 0; fb < a.n_f; fb += 64) {
@@ -262,8 +264,11 @@ __global__ __launch_bounds__(64) void nufft_wave_kernel(const float2* __restrict
         if (f < a.n_f) {
             const double kpf = kp[static_cast<size_t>(kap) * a.n_f + f];
             w = wk[static_cast<size_t>(kap) * a.n_f + f];
-            if (HILO) w = ldexpf(w, -g);
-            const float2 sv = spec[static_cast<size_t>(pair) * a.n_f + f];
+            float2 sv = spec[static_cast<size_t>(pair) * a.n_f + f];
+            if (HILO) {
+                w = ldexpf(w, -gw);
+                sv = make_float2(ldexpf(sv.x, gw - g), ldexpf(sv.y, gw - g));
+            }
             pa[f] = cscale(cmul(sv, cis(kpf * lmid)), w);
             py[f] = kpf * cell;
         }
