@@ -128,15 +128,30 @@ struct WindowWeights {
     double even[kWindowDegree][4], odd[kWindowDegree][4];
 };
 
-// mean over the blocks by their shares (none: equal ones)
-double mean_sinc(const std::vector<double>& X, const std::vector<double>& share, double x) {
-    double s = 0.0, n = 0.0;
+// sinc(X (x - s)) for s = 0 .. 7, the sine turned by X from each to the next
+void sincs(double X, double x, double (&out)[8]) {
+    const double cs = std::cos(X), sn = std::sin(X);
+    double c = std::cos(X * x), v = std::sin(X * x);
+    for (int s = 0; s < 8; ++s) {
+        const double y = X * (x - s);
+        out[s] = std::fabs(y) < 1e-6 ? 1.0 - y * y / 6.0 : v / y;
+        const double t = c * cs + v * sn;
+        v = v * cs - c * sn;
+        c = t;
+    }
+}
+
+// their means over the blocks by the blocks' shares (none: equal ones)
+void mean_sincs(const std::vector<double>& X, const std::vector<double>& share, double x, double (&out)[8]) {
+    double n = 0.0, v[8];
+    for (double& o : out) o = 0.0;
     for (size_t b = 0; b < X.size(); ++b) {
-        const double y = X[b] * x, f = share.empty() ? 1.0 : share[b];
-        s += f * (std::fabs(y) < 1e-6 ? 1.0 - y * y / 6.0 : std::sin(y) / y);
+        const double f = share.empty() ? 1.0 : share[b];
+        sincs(X[b], x, v);
+        for (int s = 0; s < 8; ++s) out[s] += f * v[s];
         n += f;
     }
-    return s / n;
+    for (double& o : out) o /= n;
 }
 
 // b = A^-1 b by elimination with row exchanges
@@ -163,14 +178,14 @@ void solve(double (&A)[N][N], double (&b)[N]) {
 void window_design(const std::vector<double>& X, const std::vector<double>& share, double xm, WindowWeights* out) {
     constexpr int D = kWindowDegree;
     double g[8];   // mean sinc at whole sample distances
-    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, share, d);
+    mean_sincs(X, share, 0.0, g);
     const double ym = xm * xm;
     double node[D], E[D][4], O[D][4];
     for (int i = 0; i < D; ++i) {
         node[i] = std::cos(kPi * (i + 0.5) / D);
         const double x = std::sqrt(0.5 * (1.0 + node[i]) * ym);
         double b[8];
-        for (int s = 0; s < 8; ++s) b[s] = mean_sinc(X, share, x - (s - 3.5));
+        mean_sincs(X, share, x + 3.5, b);
         for (int par = 0; par < 2; ++par) {
             const double sg = par ? -1.0 : 1.0;
             double A[4][4], r[4];
@@ -196,63 +211,68 @@ void window_design(const std::vector<double>& X, const std::vector<double>& shar
         }
 }
 
-// rms error of these weights over the positions |x| <= xm and the bands X,
-// polynomials included
-double window_error(const std::vector<double>& X, double xm, const WindowWeights& wt) {
-    constexpr int D = kWindowDegree;
-    const double ym = xm * xm;
-    double g[8];
-    for (int d = 0; d < 8; ++d) g[d] = mean_sinc(X, {}, d);
-    double err = 0.0;
-    constexpr int NX = 9;
-    for (int i = 0; i < NX; ++i) {
-        const double x = xm * (i + 0.5) / NX, z = 2.0 * x * x / ym - 1.0;
-        double w[8], e = 1.0;
-        for (int s = 0; s < 4; ++s) {
-            double ev = 0.0, od = 0.0;
-            for (int k = D - 1; k >= 0; --k) {
-                ev = ev * z + wt.even[k][s];
-                od = od * z + wt.odd[k][s];
-            }
-            w[s] = ev + x * od;
-            w[7 - s] = ev - x * od;
+// The eight weights at position x.
+void window_weights(const WindowWeights& wt, double x, double xm, double (&w)[8]) {
+    const double z = 2.0 * x * x / (xm * xm) - 1.0;
+    for (int s = 0; s < 4; ++s) {
+        double ev = 0.0, od = 0.0;
+        for (int k = kWindowDegree - 1; k >= 0; --k) {
+            ev = ev * z + wt.even[k][s];
+            od = od * z + wt.odd[k][s];
         }
-        for (int s = 0; s < 8; ++s) {
-            e -= 2.0 * w[s] * mean_sinc(X, {}, x - (s - 3.5));
-            for (int t = 0; t < 8; ++t) e += w[s] * w[t] * g[std::abs(s - t)];
-        }
-        err += std::max(e, 0.0);
+        w[s] = ev + x * od;
+        w[7 - s] = ev - x * od;
     }
-    return std::sqrt(err / NX);
 }
 
-// Squared error of these weights at n phase steps per sample th[i], mean over
-// the positions |x| <= xm, polynomials included.
-void window_error(const double* th, int n, double xm, const WindowWeights& wt, double* e2) {
-    constexpr int D = kWindowDegree, NX = 9;
-    for (int i = 0; i < n; ++i) e2[i] = 0.0;
-    for (int j = 0; j < NX; ++j) {
-        const double x = xm * (j + 0.5) / NX, z = 2.0 * x * x / (xm * xm) - 1.0;
-        double w[8];
-        for (int s = 0; s < 4; ++s) {
-            double ev = 0.0, od = 0.0;
-            for (int k = D - 1; k >= 0; --k) {
-                ev = ev * z + wt.even[k][s];
-                od = od * z + wt.odd[k][s];
-            }
-            w[s] = ev + x * od;
-            w[7 - s] = ev - x * od;
+// Squared error of these weights in each block's band, mean over the positions
+// |x| <= xm, polynomials included: sums of sinc(X_b (s - s')) and
+// sinc(X_b (x - s)) as in the design.
+std::vector<double> window_error(const std::vector<double>& X, double xm, const WindowWeights& wt) {
+    constexpr int NX = 9;
+    std::vector<double> e2(X.size(), 0.0);
+    for (int i = 0; i < NX; ++i) {
+        const double x = xm * (i + 0.5) / NX;
+        double w[8], lag[8] = {}, g[8], v[8];   // lag[d]: products of weights d samples apart
+        window_weights(wt, x, xm, w);
+        for (int s = 0; s < 8; ++s)
+            for (int t = 0; t < 8; ++t) lag[std::abs(s - t)] += w[s] * w[t];
+        for (size_t b = 0; b < X.size(); ++b) {
+            sincs(X[b], 0.0, g);
+            sincs(X[b], x + 3.5, v);
+            double e = 1.0;
+            for (int s = 0; s < 8; ++s) e += lag[s] * g[s] - 2.0 * w[s] * v[s];
+            e2[b] += std::max(e, 0.0) / NX;
         }
-        for (int i = 0; i < n; ++i) {
+    }
+    return e2;
+}
+
+// rms of the first n squared errors
+double rms(const std::vector<double>& e2, size_t n) {
+    double s = 0.0;
+    for (size_t b = 0; b < n; ++b) s += e2[b];
+    return std::sqrt(s / static_cast<double>(n));
+}
+
+// Their squared error at n phase steps per sample th[i], mean over the same
+// positions.
+void window_error(const double* th, int n, double xm, const WindowWeights& wt, double* e2) {
+    constexpr int NX = 5;
+    double w[NX][8];
+    for (int j = 0; j < NX; ++j) window_weights(wt, xm * (j + 0.5) / NX, xm, w[j]);
+    for (int i = 0; i < n; ++i) {
+        const double cs = std::cos(th[i]), sn = std::sin(th[i]);
+        e2[i] = 0.0;
+        for (int j = 0; j < NX; ++j) {
             // sum_s w_s e^{j th (s - 3.5 - x)} - 1 by the powers of e^{j th}
-            const double cs = std::cos(th[i]), sn = std::sin(th[i]);
             double re = 0.0, im = 0.0;
             for (int s = 7; s >= 0; --s) {
-                const double t = re * cs - im * sn + w[s];
+                const double t = re * cs - im * sn + w[j][s];
                 im = re * sn + im * cs;
                 re = t;
             }
-            const double ph = th[i] * (x + 3.5), c0 = std::cos(ph), s0 = std::sin(ph);
+            const double ph = th[i] * (xm * (j + 0.5) / NX + 3.5), c0 = std::cos(ph), s0 = std::sin(ph);
             const double dr = re * c0 + im * s0 - 1.0, di = im * c0 - re * s0;
             e2[i] += (dr * dr + di * di) / NX;
         }
@@ -277,14 +297,14 @@ void window_error(const double* th, int n, double xm, const WindowWeights& wt, d
 // aperture sees, from 0 up: with equal shares the image was less exact than
 // the B-spline path's where the lowest blocks are much narrower than the rest
 // (10 of 278 problems of 72 .. 512 scan positions and 2.2 .. 5.6 mm pixels, by
-// up to 2.06, all but two of them with a 3 mm scan step; an echo at k_z = 0
+// up to 2.06, eight of them with a 3 mm scan step; an echo at k_z = 0
 // alone by up to 3.7).  Shares h_b^(-8 gamma) (h_b the block's half band) trade
 // error of the wide bands for the narrow ones'.  For each gamma both forms'
 // squared errors are summed over the k' of every propagating (frequency, bin),
 // in the blocks each form has, from k_z = 0 up to six fractions of |k_z|; the
 // first gamma at which the largest of the six ratios is below 0.9 is taken, or
 // the one where it is smallest, which has to be at most 1.05 (9 of the 278 keep
-// the other plan).  The 269 have 0.35 of the B-spline path's error in the mean,
+// the other plan).  The 269 have 0.34 of the B-spline path's error in the mean,
 // two of them more than it (1.5e-6 against 1.2e-6, 2.0e-6 against 1.5e-6).
 //
 // base: the call's plan in FP32; held: the plan that runs otherwise.
@@ -373,8 +393,8 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
         const double xm = 0.5 * (spans[i] + step) + 0.02;
         p.win_z = 2.0 / (xm * xm);
         window_design(X, {}, xm, &w);
-        return window_error(X, xm, w) <= (step == 2 ? 0.55 : 0.9) * base_err &&
-               window_error({X.begin(), X.begin() + n_low}, xm, w) <= 1.5 * base_low;
+        const std::vector<double> e2 = window_error(X, xm, w);
+        return rms(e2, e2.size()) <= (step == 2 ? 0.55 : 0.9) * base_err && rms(e2, n_low) <= 1.5 * base_low;
     };
     bool found = false;
     for (int step = 2; step >= 1 && !found; --step) {
@@ -391,13 +411,13 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
 
     // the shares (see above)
     constexpr double kBelow = 0.9, kMost = 1.05;
-    constexpr int kPhase = 48;   // cells of |k'|
+    constexpr int kPhase = 32;   // cells of |k'|
     const double fraction[6] = {0.125, 0.25, 0.375, 0.5, 0.75, 1.0};
     double count[6][kPhase] = {}, spline[6] = {}, th[kPhase], e2[kPhase];
     for (int i = 0; i < kPhase; ++i) th[i] = (i + 0.5) / kPhase * p.half_band * p.du;
     const int last = p.n_z / 2;   // bins m = 0 .. last and -m
-    const int fs = std::max(1, p.n_f / 8);
-    for (int m = 0; m <= last; ++m) {
+    const int fs = std::max(1, p.n_f / 8), ms = std::max(1, last / 64);   // some 8 frequencies, 64 to 128 bins
+    for (int m = 0; m <= last; m += ms) {
         const double kz = 2.0 * kPi * m / (p.n_z * g->scan_step), q = 0.25 * kz * kz;
         int part = 0;
         while (part < 5 && m > fraction[part] * last) ++part;
@@ -420,8 +440,8 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     for (double gamma : {0.0, 0.5, 0.75, 1.0, 1.25, 1.5, 1.75, 2.0, 2.5}) {
         std::vector<double> share;
         for (double h : half) share.push_back(std::pow(std::max(h / p.half_band, 0.25), -8.0 * gamma));
-        WindowWeights t;
-        window_design(X, share, xm, &t);
+        WindowWeights t = w;   // equal shares: as the step was chosen
+        if (gamma > 0) window_design(X, share, xm, &t);
         window_error(th, kPhase, xm, t, e2);
         double worst = 0.0, sw = 0.0, ss = 0.0;
         for (int i = 0; i < 6; ++i) {
@@ -578,13 +598,13 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
             for (int kap = b * p.block; kap < std::min(p.n_z, (b + 1) * p.block); ++kap) {
                 const int sk = kap < (p.n_z + 1) / 2 ? kap : kap - p.n_z;
                 const double kz = 2.0 * kPi * sk / (p.n_z * g->scan_step);
-                for (int f = 0; f < p.n_f; ++f) {
-                    const double arg = g->k[f] * g->k[f] - 0.25 * kz * kz;
-                    if (arg <= 0) continue;
-                    const double kr = std::sqrt(arg);
-                    lo = std::min(lo, kr);
-                    hi = std::max(hi, kr);
-                }
+                // k_rho rises with f: its extremes are those of the first
+                // propagating frequency and the last
+                auto arg = [&](double k) { return k * k - 0.25 * kz * kz; };
+                if (arg(g->k[p.n_f - 1]) <= 0) continue;
+                const double kf = *std::partition_point(g->k.begin(), g->k.end(), [&](double k) { return arg(k) <= 0; });
+                lo = std::min(lo, std::sqrt(arg(kf)));
+                hi = std::max(hi, std::sqrt(arg(g->k[p.n_f - 1])));
             }
             if (hi < lo) {
                 p.kref[b] = 0.0;
