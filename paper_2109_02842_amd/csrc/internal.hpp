@@ -34,8 +34,8 @@ constexpr double kNufftUpsample = 1.25;  // FP32 NUFFT: fine grid of at least 1.
 constexpr int kWindowBins = 32;
 constexpr int kWindowDegree = 5;
 constexpr int kSpectrumMaxParts = 256;
-constexpr int kMaxWindowPieces = 512;      // partial spectra of split items (16x16 pixels x 64 rows)
-constexpr size_t kWindowPieceBytes = 16ull * 16 * 2 * kWindowBins * 8;
+constexpr int kWindowSlots = 512;          // its resident workgroups: two on each of 256 CUs
+constexpr size_t kWindowPieceBytes = 16ull * 16 * 2 * kWindowBins * 8;   // a piece of a split item: 16x16 pixels x 64 rows
 constexpr int kMaxGL = 32;          // positive quadrature nodes for the kernel transform
 constexpr int kMaxRadices = 16;
 

@@ -598,7 +598,8 @@ int check_window_plan(const HybridPlan& p) {
 
 // Tail split, as in the other matrix-core back-projection: the items beyond
 // the last full round of resident workgroups, if at most half a round, run
-// in pieces over their channel pairs that fill it.
+// in pieces over their channel pairs that fill it, as far as the workspace
+// holds their partial spectra (planned for kWindowSlots workgroups).
 int split_tail(const HybridPlan& p, WinArgs* a) {
     long long slots = 0;
     if (int rc = window_slots(p.window / 4, p.win_step, p.mode == PL_MONO, false, &slots)) return rc;

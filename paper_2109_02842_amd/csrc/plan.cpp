@@ -491,19 +491,20 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     // |q| <= n_f k_max sqrt(2) (largest |S| part), a tenth for the NUFFT's error
     p.log2_gain = static_cast<int>(std::ceil(std::log2(1.6 * p.n_f * g->k[p.n_f - 1])));
 
-    // split items' partial spectra: as many pieces as the tail split can ask
-    // for, within what the workspace of make_plan's plan or the static
-    // scratch holds already where that is the limit
+    // split items' partial spectra: those of the launch's tail split on the
+    // card's kWindowSlots resident workgroups, none where it splits nothing,
+    // and no more than the static scratch has left beside a problem it holds
     p.part_pieces = 0;
     if (set_layout(&p)) return false;
-    const long long items = static_cast<long long>(p.tiles_x) * p.tiles_y * p.n_blocks;
-    long long pieces = std::min<long long>(kMaxWindowPieces, items * ((p.n_ch + 1) / 2));
+    const long long items = static_cast<long long>(p.tiles_x) * p.tiles_y * p.n_blocks, tail = items % kWindowSlots;
+    long long pieces = 0;   // per split item
+    if (tail > 0 && 2 * tail <= kWindowSlots) pieces = std::min<long long>(kWindowSlots / tail, (p.n_ch + 1) / 2);
     const size_t scratch = static_cast<size_t>(PL_STATIC_SCRATCH_BYTES);
     if (held.total <= scratch) {
         if (p.total > scratch) return false;
-        pieces = std::min<long long>(pieces, (scratch - p.total) / kWindowPieceBytes);
+        if (pieces) pieces = std::min<long long>(pieces, (scratch - p.total) / kWindowPieceBytes / tail);
     }
-    p.part_pieces = static_cast<int>(pieces);
+    p.part_pieces = pieces >= 2 ? static_cast<int>(tail * pieces) : 0;
     if (set_layout(&p)) return false;
     *out = p;
     return true;
