@@ -403,7 +403,8 @@ int reconstruct_hybrid_static(const pl_geometry* geom, const pl_image_grid* grid
  * grid and options only.  reconstruct_hybrid_prepared is reconstruct_hybrid
  * without that step: ws must hold the tables of a hybrid_prepare call with
  * the same geometry, grid and options on the same device, and no other call
- * may have used ws since (the reconstruction itself leaves them intact).
+ * may have used ws since, except the reconstruction itself and adjoint_hybrid
+ * and the steps with the same arguments, which leave the tables intact.
  * Results are bitwise those of reconstruct_hybrid.  Same errors.
  */
 int hybrid_prepare(const pl_geometry* geom, const pl_image_grid* grid, const pl_hybrid_opts* opts, void* ws,

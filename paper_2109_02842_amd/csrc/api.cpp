@@ -12,11 +12,11 @@ bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) 
 
 // stage: the single-stage entry points exchange complex64 range profiles,
 // which only the VALU back-projection reads; they plan without the
-// matrix-core back-projection.  whole: a whole reconstruction, which may take
-// the window back-projection (make_call_plan).
+// matrix-core back-projection.  use: whole reconstructions may take the window
+// back-projection (make_call_plan).
 int prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, void* ws, size_t ws_bytes,
             HybridPlan* p, DeviceTables* dt, const char* what, hipStream_t stream, bool stage = false,
-            bool upload = true, bool whole = false) {
+            bool upload = true, PlanUse use = PlanUse::kSteps) {
     pl_hybrid_opts o{};
     if (opts) o = *opts;
     if (stage) {
@@ -24,7 +24,7 @@ int prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opt
             return fail(PL_EUNSUPPORTED, "%s: the MFMA back-projection runs only inside reconstruct_hybrid", what);
         o.mfma_backprojection = -1;
     }
-    int rc = cached_plan(g, grid, whole ? opts : &o, whole, p);
+    int rc = cached_plan(g, grid, use == PlanUse::kSteps ? &o : opts, use, p);
     if (rc) return rc;
     if (!ws) return fail(PL_EWORKSPACE, "%s: null workspace", what);
     if (!aligned256(ws)) return fail(PL_EWORKSPACE, "%s: workspace must be 256-byte aligned", what);
@@ -55,7 +55,7 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     clear_error();
     if (!info) return fail(PL_EINVAL, "hybrid_plan_info: null info");
     HybridPlan p;
-    const int rc = cached_plan(g, grid, opts, false, &p);
+    const int rc = cached_plan(g, grid, opts, PlanUse::kSteps, &p);
     if (rc) return rc;
     info->n_kz = p.n_z;
     info->n_l = p.n_l;
@@ -72,7 +72,7 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     info->du = p.du;
     info->beta = p.beta;
     HybridPlan call;
-    if (const int rc2 = cached_plan(g, grid, opts, true, &call)) return rc2;
+    if (const int rc2 = cached_plan(g, grid, opts, PlanUse::kCall, &call)) return rc2;
     info->workspace_bytes = call.need;
     info->range_method = p.range_method;
     info->dk_uniform = p.range_method == PL_RANGE_RESAMPLE ? p.dkl : 0.0;
@@ -88,7 +88,7 @@ int hybrid_workspace_bytes(const pl_geometry* g, const pl_image_grid* grid, cons
     clear_error();
     if (!bytes) return fail(PL_EINVAL, "hybrid_workspace_bytes: null output");
     HybridPlan p;
-    const int rc = cached_plan(g, grid, opts, true, &p);
+    const int rc = cached_plan(g, grid, opts, PlanUse::kCall, &p);
     if (rc) return rc;
     *bytes = p.need;
     return PL_OK;
@@ -191,12 +191,12 @@ namespace pl {
 // caller prepared the workspace with hybrid_prepare for the same arguments).
 int reconstruct_impl(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, const float* echo,
                      float* image, void* ws, size_t ws_bytes, hipEvent_t* ev, hipStream_t stream, bool tables,
-                     bool upload, const char* what) {
+                     bool upload, PlanUse use, const char* what) {
     clear_error();
     if (!echo || !image) return fail(PL_EINVAL, "%s: null echo or image", what);
     HybridPlan p;
     DeviceTables dt;
-    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, what, stream, false, upload, true);
+    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, what, stream, false, upload, use);
     if (rc) return rc;
     auto mark = [&](int i) -> int {
         if (ev && ev[i] && hipEventRecord(ev[i], stream) != hipSuccess)
@@ -240,13 +240,13 @@ int reconstruct_hybrid_events(const pl_geometry* g, const pl_image_grid* grid, c
                               const float* echo, float* image, void* ws, size_t ws_bytes, hipEvent_t* ev,
                               hipStream_t stream) {
     return pl::reconstruct_impl(g, grid, opts, echo, image, ws, ws_bytes, ev, stream, true, true,
-                                "reconstruct_hybrid_events");
+                                pl::PlanUse::kCall, "reconstruct_hybrid_events");
 }
 
 int reconstruct_hybrid(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, const float* echo,
                        float* image, void* ws, size_t ws_bytes, hipStream_t stream) {
     return pl::reconstruct_impl(g, grid, opts, echo, image, ws, ws_bytes, nullptr, stream, true, true,
-                                "reconstruct_hybrid");
+                                pl::PlanUse::kCall, "reconstruct_hybrid");
 }
 
 int hybrid_prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, void* ws,
@@ -255,7 +255,7 @@ int hybrid_prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hyb
     clear_error();
     HybridPlan p;
     DeviceTables dt;
-    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, "hybrid_prepare", stream, false, true, true);
+    int rc = prepare(g, grid, opts, ws, ws_bytes, &p, &dt, "hybrid_prepare", stream, false, true, PlanUse::kCall);
     if (rc) return rc;
     return launch_plan_tables(p, dt, static_cast<char*>(ws), stream);
 }
@@ -263,7 +263,7 @@ int hybrid_prepare(const pl_geometry* g, const pl_image_grid* grid, const pl_hyb
 int reconstruct_hybrid_prepared(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,
                                 const float* echo, float* image, void* ws, size_t ws_bytes, hipStream_t stream) {
     return pl::reconstruct_impl(g, grid, opts, echo, image, ws, ws_bytes, nullptr, stream, false, true,
-                                "reconstruct_hybrid_prepared");
+                                pl::PlanUse::kCall, "reconstruct_hybrid_prepared");
 }
 
 int adjoint_hybrid(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, const float* image,

@@ -69,7 +69,7 @@ int make_hybrid_batch(int32_t n, const pl_geometry* const* geoms, const pl_image
     size_t off = 0;
     for (int s = 0; s < n; ++s) {
         if (!geoms[s]) return bail(fail(PL_EINVAL, "make_hybrid_batch: scan %d has no geometry", s));
-        int rc = cached_plan(geoms[s], &grids[s], opts ? &opts[s] : nullptr, true, &b->plans[s]);
+        int rc = cached_plan(geoms[s], &grids[s], opts ? &opts[s] : nullptr, PlanUse::kCallAlone, &b->plans[s]);
         if (rc) return bail(rc);
         b->ws_off[s] = off;
         off = align256(off + b->plans[s].total);

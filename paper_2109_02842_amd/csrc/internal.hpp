@@ -127,6 +127,11 @@ struct HybridPlan {
     size_t need = 0;  // bytes a caller's workspace must hold: the larger of the call's plans
 };
 
+// What a plan is for: the steps and the adjoint (make_plan), a whole
+// reconstruction in a caller's workspace, or one in a workspace that only
+// whole reconstructions use (make_call_plan).
+enum class PlanUse { kSteps, kCall, kCallAlone };
+
 }  // namespace pl
 
 struct pl_geometry {
@@ -148,7 +153,7 @@ struct pl_geometry {
     struct CachedPlan {
         pl_image_grid grid;
         pl_hybrid_opts opts;
-        bool whole;   // make_call_plan's, else make_plan's
+        pl::PlanUse use;
         pl::HybridPlan plan;
     };
     static constexpr size_t kPlanCache = 8;
@@ -209,19 +214,23 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
 // The plan of a whole reconstruction: the window back-projection's where the
 // options leave the kernel open and its error estimate allows it, else
 // make_plan's (which the stage calls, the adjoint and hybrid_plan_info use).
-int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* p);
-// make_plan, or with whole make_call_plan, through the geometry's cache of plans.
-int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, bool whole, HybridPlan* p);
+// In a caller's workspace its tables lie past make_plan's layout, so that the
+// adjoint or a step between hybrid_prepare and a prepared call leaves them.
+int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, bool own_workspace,
+                   HybridPlan* p);
+// Either through the geometry's cache of plans.
+int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, PlanUse use, HybridPlan* p);
 size_t backproject_window_lds_bytes(int chunks);
 
 // The hybrid reconstruction (reconstruct_hybrid and its variants): tables =
 // false skips the plan-table step (ws prepared by hybrid_prepare); upload =
 // false takes the geometry's device tables as already uploaded (no
-// allocation; PL_EINVAL if they are not); what names the entry point in
-// error messages; ev: optional stage events.
+// allocation; PL_EINVAL if they are not); use: kCall, or kCallAlone for the
+// static scratch; what names the entry point in error messages; ev: optional
+// stage events.
 int reconstruct_impl(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, const float* echo,
                      float* image, void* ws, size_t ws_bytes, hipEvent_t* ev, hipStream_t stream, bool tables,
-                     bool upload, const char* what);
+                     bool upload, PlanUse use, const char* what);
 
 // ---------------------------------------------------------- launchers
 int launch_plan_tables(const HybridPlan& p, const DeviceTables& dt, char* ws, hipStream_t s);

@@ -73,8 +73,9 @@ int set_spreading(HybridPlan* plan, double sigma) {
     return PL_OK;
 }
 
-// Workspace layout (byte offsets) of the plan.
-int set_layout(HybridPlan* plan) {
+// Workspace layout (byte offsets) of the plan: what a call writes first, then
+// its tables, from byte tables_from on if that is later.
+int set_layout(HybridPlan* plan, size_t tables_from = 0) {
     HybridPlan& p = *plan;
     const size_t nch = p.n_ch, nz = p.n_z, nf = p.n_f, npix = static_cast<size_t>(p.nx) * p.ny;
     size_t off = 0;
@@ -86,6 +87,11 @@ int set_layout(HybridPlan* plan) {
     p.off_spec = take(nch * nz * nf * 8);
     p.off_q = take(nch * nz * static_cast<size_t>(p.n_l) * 8);
     p.off_G = take(npix * nz * 8);
+    p.off_part = take(p.bp_window ? p.part_pieces * kWindowPieceBytes : backproject_mfma_part_bytes(p));
+    p.off_smax = take(p.bp_window ? kSpectrumMaxParts * sizeof(float) : 0);
+    off = std::max(off, align256(tables_from));
+    // not the last table: the window form reads a carrier's 8 bytes as 16
+    p.off_tiles = take(tile_table_bytes(p));
     p.off_llo = take(nch * 8);
     p.off_lref = take(nch * 8);
     p.off_zfft = take(p.zfft.bytes);
@@ -94,9 +100,6 @@ int set_layout(HybridPlan* plan) {
     p.off_kp = take(nz * nf * 8);
     p.off_wk = take(nz * nf * 4);
     p.off_krz = take(nz * 8);
-    p.off_tiles = take(tile_table_bytes(p));
-    p.off_part = take(p.bp_window ? p.part_pieces * kWindowPieceBytes : backproject_mfma_part_bytes(p));
-    p.off_smax = take(p.bp_window ? kSpectrumMaxParts * sizeof(float) : 0);
     p.n_chp = (p.n_ch + 31) / 32 * 32;
     p.n_fp = (p.n_f + 15) / 16 * 16;
     if (p.precision != PL_PREC_FP32) {
@@ -307,9 +310,11 @@ void window_error(const double* th, int n, double xm, const WindowWeights& wt, d
 // the other plan).  The 269 have 0.34 of the B-spline path's error in the mean,
 // two of them more than it (1.5e-6 against 1.2e-6, 2.0e-6 against 1.5e-6).
 //
-// base: the call's plan in FP32; held: the plan that runs otherwise.
+// base: the call's plan in FP32; held: the plan that runs otherwise.  own_workspace:
+// one that only such calls use; else the tables lie past all that
+// other calls with the same arguments (the adjoint, the steps) write.
 bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPlan& base, const HybridPlan& held,
-                 HybridPlan* out) {
+                 bool own_workspace, HybridPlan* out) {
     if (base.precision != PL_PREC_FP32 || base.range_method != PL_RANGE_NUFFT || base.ref_mode != PL_REF_BAND_CENTRE ||
         base.interp != PL_INTERP_BSPLINE4 || base.sigma_l > 6.0 || base.force_tile || base.force_tile_y ||
         base.force_kpl || base.force_waves || base.force_kb || base.force_bp_mfma)
@@ -505,7 +510,7 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
         if (pieces) pieces = std::min<long long>(pieces, (scratch - p.total) / kWindowPieceBytes / tail);
     }
     p.part_pieces = pieces >= 2 ? static_cast<int>(tail * pieces) : 0;
-    if (set_layout(&p)) return false;
+    if (set_layout(&p, own_workspace ? 0 : held.total)) return false;
     *out = p;
     return true;
 }
@@ -857,7 +862,8 @@ int make_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_o
     return PL_OK;
 }
 
-int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, HybridPlan* out) {
+int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, bool own_workspace,
+                   HybridPlan* out) {
     if (int rc = make_plan(g, grid, opts, out)) return rc;
     // The BF16 and FP16 modes with split operands (or the vector
     // back-projection) take the window form of their FP32 plan: it is the
@@ -877,7 +883,7 @@ int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hyb
             return PL_OK;
         }
     }
-    if (window_plan(g, grid, base, *out, &w)) {
+    if (window_plan(g, grid, base, *out, own_workspace, &w)) {
         w.need = std::max(w.total, out->total);
         *out = w;
     }
@@ -888,15 +894,18 @@ int make_call_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hyb
 static_assert(sizeof(pl_image_grid) == 2 * sizeof(int32_t) + 4 * sizeof(double), "padding in pl_image_grid");
 static_assert(sizeof(pl_hybrid_opts) == 10 * sizeof(int32_t) + 2 * sizeof(double), "padding in pl_hybrid_opts");
 
-int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, bool whole,
+int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, PlanUse use,
                 HybridPlan* out) {
-    auto plan = [&] { return whole ? make_call_plan(g, grid, opts, out) : make_plan(g, grid, opts, out); };
+    auto plan = [&] {
+        return use == PlanUse::kSteps ? make_plan(g, grid, opts, out)
+                                      : make_call_plan(g, grid, opts, use == PlanUse::kCallAlone, out);
+    };
     if (!g || !grid || !out) return plan();                         // its error
     const pl_hybrid_opts key = opts ? *opts : pl_hybrid_opts{};     // no options: all zero
     {
         std::lock_guard<std::mutex> lock(g->plan_mu);
         for (const auto& c : g->plans)
-            if (c.whole == whole && !std::memcmp(&c.grid, grid, sizeof(*grid)) &&
+            if (c.use == use && !std::memcmp(&c.grid, grid, sizeof(*grid)) &&
                 !std::memcmp(&c.opts, &key, sizeof(key))) {
                 *out = c.plan;
                 return PL_OK;
@@ -905,9 +914,9 @@ int cached_plan(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid
     if (int rc = plan()) return rc;   // outside the lock; errors are not kept
     std::lock_guard<std::mutex> lock(g->plan_mu);
     if (g->plans.size() < pl_geometry::kPlanCache) {
-        g->plans.push_back({*grid, key, whole, *out});
+        g->plans.push_back({*grid, key, use, *out});
     } else {
-        g->plans[g->next_plan] = {*grid, key, whole, *out};
+        g->plans[g->next_plan] = {*grid, key, use, *out};
         g->next_plan = (g->next_plan + 1) % pl_geometry::kPlanCache;
     }
     return PL_OK;

@@ -47,7 +47,7 @@ extern "C" int reconstruct_hybrid_static(const pl_geometry* g, const pl_image_gr
     clear_error();
     if (!g || !grid || !echo || !image) return fail(PL_EINVAL, "reconstruct_hybrid_static: null argument");
     HybridPlan p;
-    int rc = cached_plan(g, grid, opts, true, &p);
+    int rc = cached_plan(g, grid, opts, PlanUse::kCallAlone, &p);
     if (rc) return rc;
     if (p.need > static_cast<size_t>(PL_STATIC_SCRATCH_BYTES))
         return fail(PL_EWORKSPACE,
@@ -57,5 +57,5 @@ extern "C" int reconstruct_hybrid_static(const pl_geometry* g, const pl_image_gr
     void* ws = nullptr;
     if ((rc = scratch_address(&ws))) return rc;
     return reconstruct_impl(g, grid, opts, echo, image, ws, PL_STATIC_SCRATCH_BYTES, nullptr, stream, true, false,
-                            "reconstruct_hybrid_static");
+                            PlanUse::kCallAlone, "reconstruct_hybrid_static");
 }
