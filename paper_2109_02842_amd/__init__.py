@@ -516,10 +516,19 @@ class CapturedBatch:
         return self.outs
 
 
+def vector_opts(opts: dict) -> dict:
+    """These options with the vector kernels asked for where they leave the
+    kernel open: the plan whose exact transpose adjoint_hybrid evaluates."""
+    return opts if opts.get("mfma_backprojection", 0) else dict(opts, mfma_backprojection=-1)
+
+
 def adjoint_hybrid(geom: Geometry, grid, image, out=None, ws=None, **opts):
     """Echo-shaped s~[c][m][f] = H^H g: the adjoint of reconstruct_hybrid's
-    linear map (FP32 pixel-per-lane plans)."""
+    linear map with ``mfma_backprojection=-1`` (FP32 pixel-per-lane plans).  A
+    default call may run the matrix-core form instead, whose map differs from
+    that one by both interpolation errors, some 1e-5 at most."""
     torch = _torch()
+    opts = vector_opts(opts)
     need = hybrid_workspace_bytes(geom, grid, **opts)
     ws = _ws(ws, need)
     shape = (geom.n_scan, grid.ny, grid.nx)

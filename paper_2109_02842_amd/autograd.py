@@ -8,6 +8,14 @@ Two torch.autograd.Functions pair them:
 * ``echo_model(geom, grid, image)``: s = H^H x, backward H -- the forward echo
   model of a scene given as an image-shaped reflectivity x.
 
+``adjoint_hybrid`` is the exact transpose of the vector kernels
+(``mfma_backprojection=-1``).  ``echo_model`` and ``refine`` run H on them, so
+their pairs are exact transposes.  ``reconstruct`` runs the same H as
+``reconstruct_hybrid``: a default FP32 call may take the matrix-core form, which
+is closer to the exact sum, and its gradient is then that of an operator that
+differs from it by both interpolation errors (some 1e-5 at most, relative L2);
+``mfma_backprojection=-1`` makes that pair exact too.
+
 PyTorch's convention for complex tensors (the gradient of a real loss is the
 conjugate Wirtinger derivative times 2) makes the backward of a linear map A
 the adjoint A^H applied to the incoming gradient, so both functions compose
@@ -21,13 +29,13 @@ from __future__ import annotations
 import os
 from typing import Callable, List, Optional, Tuple
 
-from . import Geometry, adjoint_hybrid, reconstruct_hybrid, _torch
+from . import Geometry, adjoint_hybrid, reconstruct_hybrid, vector_opts, _torch
 
 torch = _torch()
 
 
 class Reconstruct(torch.autograd.Function):
-    """g = H s (hybrid reconstruction); backward: H^H."""
+    """g = H s (hybrid reconstruction); backward: H^H of the vector kernels."""
 
     @staticmethod
     def forward(ctx, echo, geom, grid, opts):
@@ -40,7 +48,7 @@ class Reconstruct(torch.autograd.Function):
 
 
 class EchoModel(torch.autograd.Function):
-    """s = H^H x (echo of an image-shaped scene); backward: H."""
+    """s = H^H x (echo of an image-shaped scene); backward: H, its transpose."""
 
     @staticmethod
     def forward(ctx, image, geom, grid, opts):
@@ -49,7 +57,7 @@ class EchoModel(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad):
-        return reconstruct_hybrid(ctx.geom, ctx.grid, grad.contiguous(), **ctx.opts), None, None, None
+        return reconstruct_hybrid(ctx.geom, ctx.grid, grad.contiguous(), **vector_opts(ctx.opts)), None, None, None
 
 
 def reconstruct(geom: Geometry, grid, echo, **opts):
@@ -160,10 +168,10 @@ def refine(geom: Geometry, grid, echo, steps: int = 10, x0=None, method: str = "
            resume: bool = False, **opts) -> Tuple[object, List[float]]:
     """Least-squares refinement of an image-shaped scene x for
     min_x ||H^H x - s||^2 with the library's operators (H^H the echo model
-    ``adjoint_hybrid``, H ``reconstruct_hybrid``); see ``refine_with`` for
-    the methods, the returned residual history and checkpoint / resume."""
+    ``adjoint_hybrid``, H ``reconstruct_hybrid`` on the vector kernels, its
+    exact transpose); see ``refine_with`` for the methods, the returned residual history and checkpoint / resume."""
     shape = (geom.n_scan, grid.ny, grid.nx)
     return refine_with(lambda x: adjoint_hybrid(geom, grid, x.contiguous(), **opts),
-                       lambda r: reconstruct_hybrid(geom, grid, r.contiguous(), **opts), echo, shape, steps=steps,
+                       lambda r: reconstruct_hybrid(geom, grid, r.contiguous(), **vector_opts(opts)), echo, shape, steps=steps,
                        x0=x0, method=method, model=lambda x: echo_model(geom, grid, x, **opts),
                        checkpoint=checkpoint, resume=resume)
