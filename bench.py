@@ -31,13 +31,12 @@ FLOP_PER_TERM = 24                  # (8 + 4P) with P = 4 interpolation taps
 CPU_SHARE_THREADS = 16              # host threads that come with one GPU
 
 
-def stage_rooflines(plan, a, wl, geom, stage, args, window=False):
+def stage_rooflines(plan, a, wl, geom, stage, args):
     """Algorithmic HBM bytes (and, for the FP32 NUFFT, FLOP) of the other
     stages over their event-timed durations: the FFTs move the cube in and
     out once; range compression reads the spectrum and writes the profiles
     (FLOP per (c, k_z) pair: 5 n log2 n + n_f W 14 + 2 n_l with n = n_fine).
-    A call of the matrix-core window form has its own, coarser range grid,
-    whose sizes the plan does not report: no range compression entry then."""
+    plan: the call's own (the window form's range grid is coarser)."""
     n_pairs = geom.n_channels * a.n_scan
     npix = wl.grid.nx * wl.grid.ny
     out = {}
@@ -50,8 +49,6 @@ def stage_rooflines(plan, a, wl, geom, stage, args, window=False):
 
     hbm("scan_fft", 2 * n_pairs * a.n_freq * 8)
     hbm("kz_ifft", 2 * npix * a.n_scan * 8)
-    if window:
-        return out
     hbm("range_compress", n_pairs * (a.n_freq + plan.n_l) * 8)
     if args.precision == "fp32" and args.range_method == "nufft":
         n = plan.n_fine
@@ -62,21 +59,7 @@ def stage_rooflines(plan, a, wl, geom, stage, args, window=False):
     return out
 
 
-def takes_window(pr, torch, geom, grid, echo, opts) -> bool:
-    """Whether a whole call with these options runs the matrix-core window
-    form of the FP32 plan: its image is the FP32 call's bit for bit, and
-    differs in the last digits from that of the vector kernels, which
-    mfma_backprojection=-1 asks for."""
-    if opts.get("mfma_backprojection", 0) not in (0, 1):
-        return False
-    fp32 = dict(opts, precision="fp32", mfma_backprojection=0)
-    img = pr.reconstruct_hybrid(geom, grid, echo, **fp32)
-    if torch.equal(img, pr.reconstruct_hybrid(geom, grid, echo, **dict(fp32, mfma_backprojection=-1))):
-        return False
-    return opts.get("precision", "fp32") == "fp32" or torch.equal(img, pr.reconstruct_hybrid(geom, grid, echo, **opts))
-
-
-def bp_roofline(plan, terms: int, bp_ms: float, window=False) -> dict:
+def bp_roofline(plan, terms: int, bp_ms: float) -> dict:
     """The back-projection's algorithmic FLOP rate over its event-timed
     launch against the roof of the unit it runs on: the FP32 vector peak for
     the VALU kernels, the dense BF16 / FP16 matrix-core peak for the MFMA
@@ -85,7 +68,7 @@ def bp_roofline(plan, terms: int, bp_ms: float, window=False) -> dict:
     The window form of the FP32 path issues three 32x32x16 products per
     (4x4 pixels, 32 k_z, channel)."""
     achieved = FLOP_PER_TERM * terms / (bp_ms * 1e-3) / 1e12
-    if window:
+    if plan.bp_kernel == "window":
         return {"bound": "mfma", "achieved": achieved, "peak": BF16_MFMA_PEAK_TFLOPS,
                 "frac": achieved / BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "issued_tflops": 3 * 2 * 32 * 32 * 16 / 512 * terms / (bp_ms * 1e-3) / 1e12}
@@ -221,7 +204,7 @@ def make_timers(pr, torch, W, wl, geom, echo, img):
         """min_warm_s: keep warming up until that much wall time has passed
         as well (after seconds of host-side work the GPU starts the next
         calls below its working clock)."""
-        plan = pr.hybrid_plan_info(geom, wl.grid, **opts)
+        plan = pr.hybrid_call_info(geom, wl.grid, **opts)
         ws = pr.workspace(plan.workspace_bytes)
         # plan build (host plan + device tables), reported apart; the timed
         # calls reuse the prepared tables
@@ -340,11 +323,10 @@ def bench_c3(args, torch, pr, W):
     # the GPU timings first, the host-side checks after (see main)
     for name, opts in paths:
         ms, stage, _, med, plan = time_path(opts, steps, 2, min_warm_s=0.3)
-        win = takes_window(pr, torch, geom, wl.grid, echo, opts)
         res[name] = {"value": voxels / (ms * 1e-3), "unit": "voxels/s", "ms_per_step": ms, "median_ms": med,
-                     "steps": steps, "stages_ms": stage, "bp_kernel": "window" if win else plan.bp_kernel,
+                     "steps": steps, "stages_ms": stage, "bp_kernel": plan.bp_kernel,
                      "roofline": bp_roofline(plan, a.n_scan * wl.grid.nx * wl.grid.ny * geom.n_channels,
-                                             stage["backproject"], win)}
+                                             stage["backproject"])}
         log(f"[bench] C3 {name}: {ms:.3f} ms/step ({voxels / (ms * 1e-3):.3e} voxels/s)")
     if not args.no_variants:
         ams = time_adjoint(pr, torch, geom, wl.grid, img, steps, 2)
@@ -450,7 +432,7 @@ def main() -> int:
                 l_oversample=args.l_oversample, kz_per_lane=args.kz_per_lane, waves=args.waves,
                 mfma_backprojection=args.mfma_bp, tile_y=args.tile_y, kz_block=args.kz_block,
                 range_method=args.range_method)
-    plan = pr.hybrid_plan_info(geom, wl.grid, **opts)
+    plan = pr.hybrid_call_info(geom, wl.grid, **opts)
     img = torch.empty((a.n_scan, wl.grid.ny, wl.grid.nx), dtype=torch.complex64, device="cuda")
     log(f"[bench] plan: n_l={plan.n_l} n_fine={plan.n_fine} W={plan.kernel_width} window={plan.window} "
         f"tile={plan.tile} du={plan.du * 1e3:.3f} mm workspace={plan.workspace_bytes / 2**20:.1f} MiB")
@@ -465,8 +447,7 @@ def main() -> int:
     value = voxels / (ms * 1e-3)
     terms = a.n_scan * wl.grid.nx * wl.grid.ny * geom.n_channels
     bp_ms = stage["backproject"]
-    window = takes_window(pr, torch, geom, wl.grid, echo, opts)
-    roof = bp_roofline(plan, terms, bp_ms, window)
+    roof = bp_roofline(plan, terms, bp_ms)
     out = {
         "metric": METRIC, "value": value, "unit": "voxels/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
@@ -474,13 +455,16 @@ def main() -> int:
         "data": "synthetic",
         "config": {"workload": f"{args.config}: {describe(wl)}",
                    "path": f"hybrid-{'NUFFT' if args.range_method == 'nufft' else 'resample'} {args.precision}",
-                   "interp": args.interp, "l_oversample": args.l_oversample, "nufft_tol": 1e-6,
+                   "bp_kernel": plan.bp_kernel, "nufft_tol": 1e-6, "range_step_mm": plan.du * 1e3,
+                   # the window form's weights and range step are its own
+                   "interp": "least-squares-8" if plan.bp_kernel == "window" else args.interp,
+                   "l_oversample": None if plan.bp_kernel == "window" else args.l_oversample,
                    "tile": list(plan.tile), "kz_block": plan.block},
         "roofline": dict(roof,
-                         traffic=measured_traffic("window" if window else plan.bp_kernel, args.config, args.precision, plan.n_l),
+                         traffic=measured_traffic(plan.bp_kernel, args.config, args.precision, plan.n_l),
                          kernel="backproject", flop_per_launch=FLOP_PER_TERM * terms, avg_launch_ms=bp_ms),
         "stages_ms": stage,
-        "stages_roofline": stage_rooflines(plan, a, wl, geom, stage, args, window),
+        "stages_roofline": stage_rooflines(plan, a, wl, geom, stage, args),
         "plan_build_ms": first_ms,
     }
     # Every GPU timing of this workload first, then the checks against the
@@ -499,10 +483,9 @@ def main() -> int:
             if mbp:
                 vopts.update(tile=0, tile_y=0, kz_block=0, kz_per_lane=0, waves=0)
             vms, vstage, _, vmed, vplan = time_path(vopts, args.steps, args.warmup)
-            vwin = takes_window(pr, torch, geom, wl.grid, echo, vopts)
             out["variants"][name] = {"value": voxels / (vms * 1e-3), "ms_per_step": vms, "stages_ms": vstage,
-                                     "speedup_vs_main": ms / vms, "bp_kernel": "window" if vwin else vplan.bp_kernel,
-                                     "roofline": bp_roofline(vplan, terms, vstage["backproject"], vwin)}
+                                     "speedup_vs_main": ms / vms, "bp_kernel": vplan.bp_kernel,
+                                     "roofline": bp_roofline(vplan, terms, vstage["backproject"])}
             vopts_of[name] = vopts
             log(f"[bench] {name}: {vms:.3f} ms/step; range_compress {vstage['range_compress']:.3f} ms; "
                 f"backproject {vstage['backproject']:.3f} ms")

@@ -202,6 +202,7 @@ int simulate_echo(const pl_geometry* geom, int32_t n_scat, const double* xyz_dev
 #define PL_BP_PIXEL_LANES 1  /* VALU, one pixel per lane, weights shared via LDS */
 #define PL_BP_MFMA 2         /* matrix cores, split-BF16 operands */
 #define PL_BP_MFMA_SP 3      /* matrix cores, single-pass scaled FP16 operands */
+#define PL_BP_WINDOW 4       /* matrix cores, FP32-class window form (whole calls, see reconstruct_hybrid) */
 
 /*
  * Options of the hybrid method.  Zero-initialised fields take the defaults.
@@ -312,7 +313,7 @@ typedef struct pl_hybrid_plan_info {
     int32_t window;      /* range samples staged per pixel tile and channel      */
     int32_t tile_x;      /* back-projection pixel tile                           */
     int32_t tile_y;
-    int32_t bp_kernel;   /* back-projection kernel: PL_BP_KZ_LANES, PL_BP_PIXEL_LANES, PL_BP_MFMA, PL_BP_MFMA_SP */
+    int32_t bp_kernel;   /* back-projection kernel, PL_BP_*                            */
     int32_t waves;       /* wavefronts per back-projection workgroup             */
     double du;           /* range-grid step (m of rho_T + rho_R)                 */
     double beta;         /* exponential-of-semicircle kernel shape               */
@@ -327,13 +328,17 @@ typedef struct pl_hybrid_plan_info {
 /*
  * Plan sizes for a hybrid reconstruction (host-only).  k_ref_host, if not
  * NULL, receives n_blocks reference wavenumbers (rad/m, for the range
- * rho_T + rho_R; monostatic ranges are 2 rho).  The plan is the one of the
- * steps and the adjoint; a whole FP32 reconstruction that asks for no kernel
- * may take the matrix-core window form instead (see reconstruct_hybrid), and
- * workspace_bytes is enough for both.  Errors: PL_EINVAL, PL_EUNSUPPORTED
- * (grid or problem beyond the supported sizes).
+ * rho_T + rho_R; monostatic ranges are 2 rho).  hybrid_plan_info reports the
+ * plan of the steps and the adjoint; hybrid_call_info the one that a whole
+ * reconstruction with these options runs, which may be the window form
+ * (PL_BP_WINDOW, see reconstruct_hybrid: a block is then 32 k_z bins and their
+ * mirrors n_kz - 1 - kz).  workspace_bytes is enough for both.  Errors:
+ * PL_EINVAL, PL_EUNSUPPORTED (grid or problem beyond the supported sizes).
  */
 int hybrid_plan_info(const pl_geometry* geom, const pl_image_grid* grid,
+                     const pl_hybrid_opts* opts, pl_hybrid_plan_info* info,
+                     double* k_ref_host);
+int hybrid_call_info(const pl_geometry* geom, const pl_image_grid* grid,
                      const pl_hybrid_opts* opts, pl_hybrid_plan_info* info,
                      double* k_ref_host);
 

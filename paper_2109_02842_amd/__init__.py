@@ -25,7 +25,7 @@ PL_OK, PL_EINVAL, PL_EGEOM, PL_EDEVICE, PL_EWORKSPACE, PL_EUNSUPPORTED = 0, -1, 
 PL_MONO, PL_MULTI = 0, 1
 PRECISIONS = {"fp32": 0, "bf16": 1, "fp16": 2}
 INTERPS = {"bspline4": 0, "lagrange4": 1, "linear": 2}
-BP_KERNELS = {0: "kz-lanes", 1: "pixel-lanes", 2: "mfma", 3: "mfma-1pass"}
+BP_KERNELS = {0: "kz-lanes", 1: "pixel-lanes", 2: "mfma", 3: "mfma-1pass", 4: "window"}
 RANGE_METHODS = {"nufft": 0, "resample": 1}
 REF_MODES = {"band-centre": 0, "min-k": 1}
 WARN_ELEMENT_SPACING, WARN_SCAN_STEP = 1, 2
@@ -83,6 +83,8 @@ _SIGNATURES = {
     "check_sampling": (C.c_int, [_P, C.POINTER(ImageGridC), C.POINTER(C.c_uint32)]),
     "simulate_echo": (C.c_int, [_P, C.c_int32, _P, _P, _P, _P]),
     "hybrid_plan_info": (C.c_int, [_P, C.POINTER(ImageGridC), C.POINTER(HybridOpts),
+                                   C.POINTER(HybridPlanInfo), _P]),
+    "hybrid_call_info": (C.c_int, [_P, C.POINTER(ImageGridC), C.POINTER(HybridOpts),
                                    C.POINTER(HybridPlanInfo), _P]),
     "hybrid_workspace_bytes": (C.c_int, [_P, C.POINTER(ImageGridC), C.POINTER(HybridOpts),
                                          C.POINTER(C.c_size_t)]),
@@ -272,18 +274,27 @@ class PlanInfo:
         return self.bp_kernel in ("mfma", "mfma-1pass")
 
 
-def hybrid_plan_info(geom: Geometry, grid, **opts) -> PlanInfo:
+def _plan_info(fn, geom: Geometry, grid, opts) -> PlanInfo:
     info = HybridPlanInfo()
-    _check(lib().hybrid_plan_info(geom.handle, C.byref(_grid(grid)), C.byref(_opts(**opts)),
-                                  C.byref(info), None))
+    _check(fn(geom.handle, C.byref(_grid(grid)), C.byref(_opts(**opts)), C.byref(info), None))
     kref = (C.c_double * max(1, info.n_blocks))()
-    _check(lib().hybrid_plan_info(geom.handle, C.byref(_grid(grid)), C.byref(_opts(**opts)),
-                                  C.byref(info), C.cast(kref, _P)))
+    _check(fn(geom.handle, C.byref(_grid(grid)), C.byref(_opts(**opts)), C.byref(info), C.cast(kref, _P)))
     return PlanInfo(info.n_kz, info.n_l, info.n_fine, info.kernel_width, info.n_blocks, info.block,
                     info.window, (info.tile_x, info.tile_y), info.du, info.beta,
                     int(info.workspace_bytes), list(kref[: info.n_blocks]), BP_KERNELS[info.bp_kernel],
                     int(info.waves), {v: k for k, v in RANGE_METHODS.items()}[info.range_method],
                     float(info.dk_uniform), int(info.scan_fft_len))
+
+
+def hybrid_plan_info(geom: Geometry, grid, **opts) -> PlanInfo:
+    """The plan of the steps and the adjoint."""
+    return _plan_info(lib().hybrid_plan_info, geom, grid, opts)
+
+
+def hybrid_call_info(geom: Geometry, grid, **opts) -> PlanInfo:
+    """The plan that reconstruct_hybrid runs with these options, which may be
+    the matrix-core window form (``bp_kernel == "window"``)."""
+    return _plan_info(lib().hybrid_call_info, geom, grid, opts)
 
 
 def hybrid_workspace_bytes(geom: Geometry, grid, **opts) -> int:

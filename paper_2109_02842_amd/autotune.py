@@ -1,8 +1,9 @@
 """Autotuner for the hybrid reconstruction's launch shapes.
 
 For one (geometry, image grid, precision) it times every back-projection
-configuration the planner accepts -- the pixel-per-lane kernel with 32 or 64
-k_z bins per workgroup, the k_z-per-lane kernel with 4 or 8 wavefronts, and in
+configuration the planner accepts -- the planner's own choice (the matrix-core
+window form where it is admitted), the pixel-per-lane kernel with 32 or 64 k_z
+bins per workgroup, the k_z-per-lane kernel with 4 or 8 wavefronts, and in
 the BF16 / FP16 modes the matrix-core kernel on 16x16, 16x8 and 8x8 tiles
 with 64 or 128 k_z bins and 4 or 8 wavefronts -- on the device with hipEvents
 around whole reconstructions, and returns the fastest.  Results are kept in
@@ -22,10 +23,11 @@ import os
 import statistics
 from typing import Dict, List, Optional, Tuple
 
-from . import (PolyreconError, Geometry, hybrid_plan_info, reconstruct_hybrid, workspace, _torch)
+from . import (PolyreconError, Geometry, hybrid_call_info, reconstruct_hybrid, workspace, _torch)
 
 VALU_CANDIDATES = (
-    {},                                  # pixel per lane, 32 k_z bins
+    {},                                  # the planner's choice
+    {"kz_block": 32},                    # pixel per lane, 32 k_z bins
     {"kz_block": 64},                    # pixel per lane, 64 k_z bins
     {"kz_per_lane": 1},                  # k_z per lane, 4 wavefronts
     {"kz_per_lane": 1, "waves": 8},      # k_z per lane, 8 wavefronts
@@ -47,7 +49,7 @@ def candidates(geom: Geometry, grid, precision: str = "fp32", **fixed) -> List[d
     for c in pool:
         opts = dict(fixed, precision=precision, **c)
         try:
-            plan = hybrid_plan_info(geom, grid, **opts)
+            plan = hybrid_call_info(geom, grid, **opts)
         except PolyreconError:
             continue
         key = (plan.bp_kernel, plan.tile, plan.block, plan.waves)
@@ -90,7 +92,7 @@ def _store(path: Optional[str], cache: dict) -> None:
 def time_opts(geom: Geometry, grid, echo, opts: dict, repeats: int = 5, warmup: int = 2) -> float:
     """Median device time (ms) of reconstruct_hybrid with these options."""
     torch = _torch()
-    plan = hybrid_plan_info(geom, grid, **opts)
+    plan = hybrid_call_info(geom, grid, **opts)
     ws = workspace(plan.workspace_bytes)
     out = torch.empty((geom.n_scan, grid.ny, grid.nx), dtype=torch.complex64, device="cuda")
     for _ in range(warmup):

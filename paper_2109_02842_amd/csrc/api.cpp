@@ -44,19 +44,15 @@ int axis_tables(const pl_geometry* g, void* ws, size_t ws_bytes, hipStream_t str
     return launch_axis_fft_tables(*f, static_cast<char*>(ws), stream);
 }
 
-}  // namespace
-}  // namespace pl
-
-extern "C" {
-
-int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,
-                     pl_hybrid_plan_info* info, double* k_ref_host) {
-    using namespace pl;
+// The plan of the steps or of a whole call, and the workspace that is enough
+// for both.
+int plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts, PlanUse use,
+              pl_hybrid_plan_info* info, double* k_ref_host, const char* what) {
     clear_error();
-    if (!info) return fail(PL_EINVAL, "hybrid_plan_info: null info");
-    HybridPlan p;
-    const int rc = cached_plan(g, grid, opts, PlanUse::kSteps, &p);
-    if (rc) return rc;
+    if (!info) return fail(PL_EINVAL, "%s: null info", what);
+    HybridPlan p, call;
+    if (const int rc = cached_plan(g, grid, opts, use, &p)) return rc;
+    if (const int rc = cached_plan(g, grid, opts, PlanUse::kCall, &call)) return rc;
     info->n_kz = p.n_z;
     info->n_l = p.n_l;
     info->n_fine = p.n_fine;
@@ -66,13 +62,13 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     info->window = p.window;
     info->tile_x = p.tile_x;
     info->tile_y = p.tile_y;
-    info->bp_kernel = p.bp_mfma ? (p.bp_mfma_sp ? PL_BP_MFMA_SP : PL_BP_MFMA)
-                                : (p.bp_gather ? PL_BP_PIXEL_LANES : PL_BP_KZ_LANES);
+    info->bp_kernel = p.bp_window   ? PL_BP_WINDOW
+                      : p.bp_mfma   ? (p.bp_mfma_sp ? PL_BP_MFMA_SP : PL_BP_MFMA)
+                      : p.bp_gather ? PL_BP_PIXEL_LANES
+                                    : PL_BP_KZ_LANES;
     info->waves = p.waves;
     info->du = p.du;
     info->beta = p.beta;
-    HybridPlan call;
-    if (const int rc2 = cached_plan(g, grid, opts, PlanUse::kCall, &call)) return rc2;
     info->workspace_bytes = call.need;
     info->range_method = p.range_method;
     info->dk_uniform = p.range_method == PL_RANGE_RESAMPLE ? p.dkl : 0.0;
@@ -80,6 +76,21 @@ int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_h
     info->reserved_ = 0;
     if (k_ref_host) std::memcpy(k_ref_host, p.kref, sizeof(double) * p.n_blocks);  // n_blocks <= kMaxBlocks
     return PL_OK;
+}
+
+}  // namespace
+}  // namespace pl
+
+extern "C" {
+
+int hybrid_plan_info(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,
+                     pl_hybrid_plan_info* info, double* k_ref_host) {
+    return pl::plan_info(g, grid, opts, pl::PlanUse::kSteps, info, k_ref_host, "hybrid_plan_info");
+}
+
+int hybrid_call_info(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,
+                     pl_hybrid_plan_info* info, double* k_ref_host) {
+    return pl::plan_info(g, grid, opts, pl::PlanUse::kCall, info, k_ref_host, "hybrid_call_info");
 }
 
 int hybrid_workspace_bytes(const pl_geometry* g, const pl_image_grid* grid, const pl_hybrid_opts* opts,

@@ -473,7 +473,7 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     p.tile_x = p.tile_y = 16;
     p.tiles_x = (p.nx + 15) / 16;
     p.tiles_y = (p.ny + 15) / 16;
-    p.waves = 4;
+    p.waves = 8;
     const double reach = 2.0 * std::hypot(15.0 * grid->dx, 15.0 * grid->dy) / p.du;
     const int lead = p.win_step == 2 ? 2 : 0;   // half the rows are staged from two samples earlier
     const int chunks = std::max(8, (static_cast<int>(std::ceil(reach - p.win_span + 9.2 + p.win_step)) + 3 + lead + 3) / 4);
