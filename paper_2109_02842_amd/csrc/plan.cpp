@@ -84,10 +84,13 @@ int set_layout(HybridPlan* plan, size_t tables_from = 0) {
         off = align256(off + bytes);
         return o;
     };
-    p.off_spec = take(nch * nz * nf * 8);
+    // the window form's pieces take the place of the spectrum, which no step
+    // after the range compression reads
+    const size_t part = p.bp_window ? p.part_pieces * kWindowPieceBytes : 0;
+    p.off_spec = take(std::max(nch * nz * nf * 8, part));
     p.off_q = take(nch * nz * static_cast<size_t>(p.n_l) * 8);
     p.off_G = take(npix * nz * 8);
-    p.off_part = take(p.bp_window ? p.part_pieces * kWindowPieceBytes : backproject_mfma_part_bytes(p));
+    p.off_part = p.bp_window ? p.off_spec : take(backproject_mfma_part_bytes(p));
     p.off_smax = take(p.bp_window ? kSpectrumMaxParts * sizeof(float) : 0);
     off = std::max(off, align256(tables_from));
     // not the last table: the window form reads a carrier's 8 bytes as 16
@@ -498,7 +501,8 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
 
     // split items' partial spectra: those of the launch's tail split on the
     // card's kWindowSlots resident workgroups, none where it splits nothing,
-    // and no more than the static scratch has left beside a problem it holds
+    // and no more than the static scratch has room for (in the spectrum's
+    // place) where it holds the problem
     p.part_pieces = 0;
     if (set_layout(&p)) return false;
     const long long items = static_cast<long long>(p.tiles_x) * p.tiles_y * p.n_blocks, tail = items % kWindowSlots;
@@ -507,7 +511,8 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     const size_t scratch = static_cast<size_t>(PL_STATIC_SCRATCH_BYTES);
     if (held.total <= scratch) {
         if (p.total > scratch) return false;
-        if (pieces) pieces = std::min<long long>(pieces, (scratch - p.total) / kWindowPieceBytes / tail);
+        const size_t room = scratch - p.total + static_cast<size_t>(p.n_ch) * p.n_z * p.n_f * 8;
+        if (pieces) pieces = std::min<long long>(pieces, room / kWindowPieceBytes / tail);
     }
     p.part_pieces = pieces >= 2 ? static_cast<int>(tail * pieces) : 0;
     if (set_layout(&p, own_workspace ? 0 : held.total)) return false;

@@ -45,3 +45,12 @@ def test_split_items_hold_their_pieces(n_scan, nx, ny, n_elem):
     pairs = (3 * n_elem + 1) // 2
     assert 0 < 2 * tail <= 512
     assert whole <= vector + tables + tail * min(512 // tail, pairs) * (128 << 10)
+
+
+@pytest.mark.parametrize("n_scan,nx,ny,n_elem,n_freq", [(300, 150, 60, 40, 240), (200, 120, 90, 60, 256)])
+def test_pieces_take_the_place_of_the_spectrum(n_scan, nx, ny, n_elem, n_freq):
+    # a spectrum larger than all pieces: nothing is added for them
+    a, grid = case(n_scan, nx, ny, n_elem)
+    whole, vector, tables, items = sizes(replace(a, n_freq=n_freq), grid)
+    assert 0 < 2 * (items % 512) <= 512 and 3 * n_elem * n_scan * n_freq * 8 >= 512 * (128 << 10)
+    assert vector < whole <= vector + tables
