@@ -261,16 +261,17 @@ double rms(const std::vector<double>& e2, size_t n) {
     return std::sqrt(s / static_cast<double>(n));
 }
 
-// Their squared error at n phase steps per sample th[i], mean over the same
-// positions.
-void window_error(const double* th, int n, double xm, const WindowWeights& wt, double* e2) {
-    constexpr int NX = 5;
-    double w[NX][8];
-    for (int j = 0; j < NX; ++j) window_weights(wt, xm * (j + 0.5) / NX, xm, w[j]);
+// Their squared error at n phase steps per sample th[i], mean over the
+// positions xm (j + 1/2) / kCells by the shares at[j].
+constexpr int kCells = 9;
+void window_error(const double* th, int n, double xm, const double (&at)[kCells], const WindowWeights& wt, double* e2) {
+    double w[kCells][8];
+    for (int j = 0; j < kCells; ++j) window_weights(wt, xm * (j + 0.5) / kCells, xm, w[j]);
     for (int i = 0; i < n; ++i) {
         const double cs = std::cos(th[i]), sn = std::sin(th[i]);
         e2[i] = 0.0;
-        for (int j = 0; j < NX; ++j) {
+        for (int j = 0; j < kCells; ++j) {
+            if (at[j] == 0.0) continue;
             // sum_s w_s e^{j th (s - 3.5 - x)} - 1 by the powers of e^{j th}
             double re = 0.0, im = 0.0;
             for (int s = 7; s >= 0; --s) {
@@ -278,9 +279,33 @@ void window_error(const double* th, int n, double xm, const WindowWeights& wt, d
                 im = re * sn + im * cs;
                 re = t;
             }
-            const double ph = th[i] * (xm * (j + 0.5) / NX + 3.5), c0 = std::cos(ph), s0 = std::sin(ph);
+            const double ph = th[i] * (xm * (j + 0.5) / kCells + 3.5), c0 = std::cos(ph), s0 = std::sin(ph);
             const double dr = re * c0 + im * s0 - 1.0, di = im * c0 - re * s0;
-            e2[i] += (dr * dr + di * di) / NX;
+            e2[i] += at[j] * (dr * dr + di * di);
+        }
+    }
+}
+
+// How often a pixel's position in its group's window falls into each of the
+// cells: nine groups over the image and eight channels over the array.
+void window_positions(const pl_geometry* g, const HybridPlan& p, double xm, double (&at)[kCells]) {
+    for (double& a : at) a = 0.0;
+    const double centre = 0.5 * p.win_span - 3.5;
+    for (int i = 0; i < 8; ++i) {
+        const int c = (2 * i + 1) * p.n_ch / 16;
+        const double *t = &g->tx[2 * c], *r = &g->rx[2 * c];
+        for (int k = 0; k < 9; ++k) {
+            const int gx = (p.nx + 3) / 4 * (2 * (k % 3) + 1) / 6, gy = (p.ny + 3) / 4 * (2 * (k / 3) + 1) / 6;
+            double v[16], low = 1e300;
+            for (int q = 0; q < 16; ++q) {
+                const double x = p.x0 + (4 * gx + q % 4) * p.dx, y = p.y0 + (4 * gy + q / 4) * p.dy;
+                const double lt = std::sqrt((x - t[0]) * (x - t[0]) + (y - t[1]) * (y - t[1]));
+                const double lr = p.mode == PL_MONO ? lt : std::sqrt((x - r[0]) * (x - r[0]) + (y - r[1]) * (y - r[1]));
+                v[q] = (lt + lr) / p.du;
+                low = std::min(low, v[q]);
+            }
+            const double start = std::rint((low + centre) / p.win_step) * p.win_step;
+            for (double u : v) at[std::min(kCells - 1, static_cast<int>(std::fabs(u - start - 3.5) / xm * kCells))] += 1.0 / 1152;
         }
     }
 }
@@ -302,16 +327,19 @@ void window_error(const double* th, int n, double xm, const WindowWeights& wt, d
 // band, these weights' hardly, and an echo's energy lies at the |k_z| its
 // aperture sees, from 0 up: with equal shares the image was less exact than
 // the B-spline path's where the lowest blocks are much narrower than the rest
-// (10 of 278 problems of 72 .. 512 scan positions and 2.2 .. 5.6 mm pixels, by
-// up to 2.06, eight of them with a 3 mm scan step; an echo at k_z = 0
-// alone by up to 3.7).  Shares h_b^(-8 gamma) (h_b the block's half band) trade
-// error of the wide bands for the narrow ones'.  For each gamma both forms'
-// squared errors are summed over the k' of every propagating (frequency, bin),
-// in the blocks each form has, from k_z = 0 up to six fractions of |k_z|; the
-// first gamma at which the largest of the six ratios is below 0.9 is taken, or
-// the one where it is smallest, which has to be at most 1.05 (9 of the 278 keep
-// the other plan).  The 269 have 0.34 of the B-spline path's error in the mean,
-// two of them more than it (1.5e-6 against 1.2e-6, 2.0e-6 against 1.5e-6).
+// (16 of 368 problems of 69 .. 512 scan positions and 2.2 .. 5.6 mm pixels, by
+// up to 2.4, 11 of them with a 3 mm scan step; an echo at k_z = 0 alone in 82,
+// by up to 3.7).  Shares h_b^(-8 gamma) (h_b the block's half band) trade error
+// of the wide bands for the narrow ones'.  For each gamma both forms' squared
+// errors are summed over the k' of every propagating (frequency, bin), in the
+// blocks each form has and at the positions in the window that occur, from
+// k_z = 0 up to six fractions of |k_z|; the first gamma at which the largest of
+// the six ratios is at most 0.7 is taken, or the one where it is smallest,
+// which has to be at most 1.05 (4 of the 368, at 1.3 to 2.4 before, keep the
+// other plan).  The 364 have 0.36 of the B-spline path's error in the mean,
+// five of them more than it (1.14 .. 1.49 of errors of 1.2 .. 2.6e-6), and at
+// k_z = 0 alone 39 (up to 1.75).  With all positions alike in the estimate 10
+// of 260 were refused, most of them below 1.
 //
 // base: the call's plan in FP32; held: the plan that runs otherwise.  own_workspace:
 // one that only such calls use; else the tables lie past all that
@@ -418,7 +446,7 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     if (!found) return false;
 
     // the shares (see above)
-    constexpr double kBelow = 0.9, kMost = 1.05;
+    constexpr double kBelow = 0.7, kMost = 1.05;
     constexpr int kPhase = 32;   // cells of |k'|
     const double fraction[6] = {0.125, 0.25, 0.375, 0.5, 0.75, 1.0};
     double count[6][kPhase] = {}, spline[6] = {}, th[kPhase], e2[kPhase];
@@ -444,13 +472,14 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     std::vector<double> X;
     for (double h : half) X.push_back(h * p.du);
     const double xm = 0.5 * (p.win_span + p.win_step) + 0.02;
-    double least = 1e300;
+    double at[kCells], least = 1e300;
+    window_positions(g, p, xm, at);
     for (double gamma : {0.0, 0.5, 0.75, 1.0, 1.25, 1.5, 1.75, 2.0, 2.5}) {
         std::vector<double> share;
         for (double h : half) share.push_back(std::pow(std::max(h / p.half_band, 0.25), -8.0 * gamma));
         WindowWeights t = w;   // equal shares: as the step was chosen
         if (gamma > 0) window_design(X, share, xm, &t);
-        window_error(th, kPhase, xm, t, e2);
+        window_error(th, kPhase, xm, at, t, e2);
         double worst = 0.0, sw = 0.0, ss = 0.0;
         for (int i = 0; i < 6; ++i) {
             for (int j = 0; j < kPhase; ++j) sw += count[i][j] * e2[j];
