@@ -181,7 +181,7 @@ int launch_range_adjoint_wave(const HybridPlan& p, const float2* qt, char* ws, f
 // four wavefronts' copies are summed through LDS in a fixed order, so the
 // result is the same bit for bit on every run.
 //
-// Bound by VALU issue (91 % of the cycles, 27 instructions per pixel and
+// Bound by VALU issue (95 % of the cycles, 27 instructions per pixel and
 // wavefront, of which 12 are the term's, 5 the window's moves, 10 the tile's
 // records and the tile list).  Ranks are read from lanes, not broadcast
 // through LDS, and a monostatic range takes one float64 root: 3.48 -> 3.20 ms

@@ -26,10 +26,10 @@
 // What bounds it: the matrix cores and the VALU of a SIMD hardly overlap (a
 // few VALU instructions hide in a wavefront's own 32-cycle products, another
 // wavefront's add to them).  Per (group, channel, 64 rows) the products take
-// 6 x 32 = 192 cycles and forming B about 200, 454 in all at ~2 GHz (the
-// clock the card holds under this load).  Measured at 512 k_z x 320 channels
-// x 128x128 pixels 0.74 ms where the pixel-per-lane gather takes 1.37, and at
-// 512 x 896 x 200x200 6.5 ms (14.4).  16x16x32 products with four wavefronts
+// 6 x 32 = 192 cycles and the VALU, forming B for the most part, 235, of 400 in
+// all (counters at 256 k_z x 320 channels x 200x200 pixels).  Measured there
+// 0.72 ms where the pixel-per-lane gather takes 1.38, and at 512 x 896 x
+// 256x256 6.5 ms (14.4).  16x16x32 products with four wavefronts
 // took 0.80 ms, with eight 0.72 but more VGPRs than 32x32x16 leave; copies
 // spread over the loop, or staged through registers, changed nothing.
 //

@@ -266,7 +266,7 @@ int launch_simulate(const pl_geometry* g, const DeviceTables& dt, int n_scat, co
     a.n_z = g->n_scan;
     a.n_f = g->n_freq;
     a.n_scat = n_scat;
-    // 32 frequencies per thread share one path and its phases (about 204
+    // 32 frequencies per thread share one path and its phases (about 202
     // instructions where two threads of 16 take 272), unless 16 leave less
     // padding or 32 leave fewer than two wavefronts per SIMD.  Measured, 500
     // scatterers, 32 / 16 per thread: 64 frequencies x 81920 (channel,
