@@ -147,14 +147,37 @@ void sincs(double X, double x, double (&out)[8]) {
     }
 }
 
-// their means over the blocks by the blocks' shares (none: equal ones)
-void mean_sincs(const std::vector<double>& X, const std::vector<double>& share, double x, double (&out)[8]) {
-    double n = 0.0, v[8];
+// The blocks' sinc values that a design takes: the whole sample distances
+// from 0, and at its positions.
+constexpr int kDesignRows = kWindowDegree + 1;
+struct DesignSincs {
+    double node[kWindowDegree], x[kWindowDegree];
+    std::vector<double> v;   // [block][row][8]
+};
+
+DesignSincs design_sincs(const std::vector<double>& X, double xm) {
+    DesignSincs d;
+    for (int i = 0; i < kWindowDegree; ++i) {
+        d.node[i] = std::cos(kPi * (i + 0.5) / kWindowDegree);
+        d.x[i] = std::sqrt(0.5 * (1.0 + d.node[i]) * (xm * xm));
+    }
+    d.v.resize(X.size() * kDesignRows * 8);
+    for (size_t b = 0; b < X.size(); ++b)
+        for (int i = 0; i < kDesignRows; ++i) {
+            double row[8];
+            sincs(X[b], i ? d.x[i - 1] + 3.5 : 0.0, row);
+            std::copy(row, row + 8, &d.v[(b * kDesignRows + i) * 8]);
+        }
+    return d;
+}
+
+// means of one row over the blocks by the blocks' shares (none: equal ones)
+void mean_sincs(const DesignSincs& d, const std::vector<double>& share, int row, double (&out)[8]) {
+    double n = 0.0;
     for (double& o : out) o = 0.0;
-    for (size_t b = 0; b < X.size(); ++b) {
+    for (size_t b = 0; b < d.v.size() / (kDesignRows * 8); ++b) {
         const double f = share.empty() ? 1.0 : share[b];
-        sincs(X[b], x, v);
-        for (int s = 0; s < 8; ++s) out[s] += f * v[s];
+        for (int s = 0; s < 8; ++s) out[s] += f * d.v[(b * kDesignRows + row) * 8 + s];
         n += f;
     }
     for (double& o : out) o /= n;
@@ -181,17 +204,14 @@ void solve(double (&A)[N][N], double (&b)[N]) {
     }
 }
 
-void window_design(const std::vector<double>& X, const std::vector<double>& share, double xm, WindowWeights* out) {
+void window_design(const DesignSincs& d, const std::vector<double>& share, WindowWeights* out) {
     constexpr int D = kWindowDegree;
     double g[8];   // mean sinc at whole sample distances
-    mean_sincs(X, share, 0.0, g);
-    const double ym = xm * xm;
-    double node[D], E[D][4], O[D][4];
+    mean_sincs(d, share, 0, g);
+    double E[D][4], O[D][4];
     for (int i = 0; i < D; ++i) {
-        node[i] = std::cos(kPi * (i + 0.5) / D);
-        const double x = std::sqrt(0.5 * (1.0 + node[i]) * ym);
         double b[8];
-        mean_sincs(X, share, x + 3.5, b);
+        mean_sincs(d, share, i + 1, b);
         for (int par = 0; par < 2; ++par) {
             const double sg = par ? -1.0 : 1.0;
             double A[4][4], r[4];
@@ -201,7 +221,7 @@ void window_design(const std::vector<double>& X, const std::vector<double>& shar
                 r[s] = 0.5 * (b[s] + sg * b[7 - s]);
             }
             solve(A, r);
-            for (int s = 0; s < 4; ++s) (par ? O : E)[i][s] = par ? r[s] / x : r[s];
+            for (int s = 0; s < 4; ++s) (par ? O : E)[i][s] = par ? r[s] / d.x[i] : r[s];
         }
     }
     for (int par = 0; par < 2; ++par)
@@ -209,7 +229,7 @@ void window_design(const std::vector<double>& X, const std::vector<double>& shar
             double V[D][D], v[D];
             for (int i = 0; i < D; ++i) {
                 double pw = 1.0;
-                for (int k = 0; k < D; ++k) V[i][k] = pw, pw *= node[i];
+                for (int k = 0; k < D; ++k) V[i][k] = pw, pw *= d.node[i];
                 v[i] = (par ? O : E)[i][s];
             }
             solve(V, v);
@@ -234,17 +254,18 @@ void window_weights(const WindowWeights& wt, double x, double xm, double (&w)[8]
 // Squared error of these weights in each block's band, mean over the positions
 // |x| <= xm, polynomials included: sums of sinc(X_b (s - s')) and
 // sinc(X_b (x - s)) as in the design.
-std::vector<double> window_error(const std::vector<double>& X, double xm, const WindowWeights& wt) {
+std::vector<double> window_error(const std::vector<double>& X, const DesignSincs& d, double xm,
+                                 const WindowWeights& wt) {
     constexpr int NX = 9;
     std::vector<double> e2(X.size(), 0.0);
     for (int i = 0; i < NX; ++i) {
         const double x = xm * (i + 0.5) / NX;
-        double w[8], lag[8] = {}, g[8], v[8];   // lag[d]: products of weights d samples apart
+        double w[8], lag[8] = {}, v[8];   // lag[d]: products of weights d samples apart
         window_weights(wt, x, xm, w);
         for (int s = 0; s < 8; ++s)
             for (int t = 0; t < 8; ++t) lag[std::abs(s - t)] += w[s] * w[t];
         for (size_t b = 0; b < X.size(); ++b) {
-            sincs(X[b], 0.0, g);
+            const double* g = &d.v[b * kDesignRows * 8];
             sincs(X[b], x + 3.5, v);
             double e = 1.0;
             for (int s = 0; s < 8; ++s) e += lag[s] * g[s] - 2.0 * w[s] * v[s];
@@ -261,14 +282,33 @@ double rms(const std::vector<double>& e2, size_t n) {
     return std::sqrt(s / static_cast<double>(n));
 }
 
-// Their squared error at n phase steps per sample th[i], mean over the
-// positions xm (j + 1/2) / kCells by the shares at[j].
-constexpr int kCells = 9;
-void window_error(const double* th, int n, double xm, const double (&at)[kCells], const WindowWeights& wt, double* e2) {
+// The phase steps per sample th and, at each, the turn e^{j th} and the turns
+// at the positions x = xm (j + 1/2) / kCells from the window's first sample.
+constexpr int kCells = 9, kPhase = 32;
+struct PhaseTurns {
+    double cs[kPhase], sn[kPhase], c[kPhase][kCells], s[kPhase][kCells];
+};
+
+void phase_turns(double most, double xm, PhaseTurns* t) {
+    for (int i = 0; i < kPhase; ++i) {
+        const double th = (i + 0.5) / kPhase * most;
+        t->cs[i] = std::cos(th);
+        t->sn[i] = std::sin(th);
+        for (int j = 0; j < kCells; ++j) {
+            const double ph = th * (xm * (j + 0.5) / kCells + 3.5);
+            t->c[i][j] = std::cos(ph);
+            t->s[i][j] = std::sin(ph);
+        }
+    }
+}
+
+// The weights' squared error at each phase step, mean over the positions by
+// the shares at[j].
+void window_error(const PhaseTurns& p, double xm, const double (&at)[kCells], const WindowWeights& wt, double* e2) {
     double w[kCells][8];
     for (int j = 0; j < kCells; ++j) window_weights(wt, xm * (j + 0.5) / kCells, xm, w[j]);
-    for (int i = 0; i < n; ++i) {
-        const double cs = std::cos(th[i]), sn = std::sin(th[i]);
+    for (int i = 0; i < kPhase; ++i) {
+        const double cs = p.cs[i], sn = p.sn[i];
         e2[i] = 0.0;
         for (int j = 0; j < kCells; ++j) {
             if (at[j] == 0.0) continue;
@@ -279,7 +319,7 @@ void window_error(const double* th, int n, double xm, const double (&at)[kCells]
                 im = re * sn + im * cs;
                 re = t;
             }
-            const double ph = th[i] * (xm * (j + 0.5) / kCells + 3.5), c0 = std::cos(ph), s0 = std::sin(ph);
+            const double c0 = p.c[i][j], s0 = p.s[i][j];
             const double dr = re * c0 + im * s0 - 1.0, di = im * c0 - re * s0;
             e2[i] += at[j] * (dr * dr + di * di);
         }
@@ -428,29 +468,29 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
         // 1/64 sample and float rounding of the group's lowest position
         const double xm = 0.5 * (spans[i] + step) + 0.02;
         p.win_z = 2.0 / (xm * xm);
-        window_design(X, {}, xm, &w);
-        const std::vector<double> e2 = window_error(X, xm, w);
+        const DesignSincs values = design_sincs(X, xm);
+        window_design(values, {}, &w);
+        const std::vector<double> e2 = window_error(X, values, xm, w);
         return rms(e2, e2.size()) <= (step == 2 ? 0.55 : 0.9) * base_err && rms(e2, n_low) <= 1.5 * base_low;
     };
     bool found = false;
     for (int step = 2; step >= 1 && !found; --step) {
         if (!admitted(step, 4)) continue;   // the narrowest step
-        int lo = 0, hi = 4;                 // the error falls with the step: the first of the five admitted
+        int lo = 0, hi = 4, last = 4;       // the error falls with the step: the first of the five admitted
         while (lo < hi) {
             const int mid = (lo + hi) / 2;
+            last = mid;
             if (admitted(step, mid)) hi = mid;
             else lo = mid + 1;
         }
-        found = admitted(step, hi);
+        found = last == hi || admitted(step, hi);
     }
     if (!found) return false;
 
     // the shares (see above)
     constexpr double kBelow = 0.7, kMost = 1.05;
-    constexpr int kPhase = 32;   // cells of |k'|
     const double fraction[6] = {0.125, 0.25, 0.375, 0.5, 0.75, 1.0};
-    double count[6][kPhase] = {}, spline[6] = {}, th[kPhase], e2[kPhase];
-    for (int i = 0; i < kPhase; ++i) th[i] = (i + 0.5) / kPhase * p.half_band * p.du;
+    double count[6][kPhase] = {}, spline[6] = {}, e2[kPhase];   // kPhase cells of |k'|
     const int last = p.n_z / 2;   // bins m = 0 .. last and -m
     const int fs = std::max(1, p.n_f / 8), ms = std::max(1, last / 64);   // some 8 frequencies, 64 to 128 bins
     for (int m = 0; m <= last; m += ms) {
@@ -474,12 +514,15 @@ bool window_plan(const pl_geometry* g, const pl_image_grid* grid, const HybridPl
     const double xm = 0.5 * (p.win_span + p.win_step) + 0.02;
     double at[kCells], least = 1e300;
     window_positions(g, p, xm, at);
+    const DesignSincs values = design_sincs(X, xm);
+    PhaseTurns turns;
+    phase_turns(p.half_band * p.du, xm, &turns);
     for (double gamma : {0.0, 0.5, 0.75, 1.0, 1.25, 1.5, 1.75, 2.0, 2.5}) {
         std::vector<double> share;
         for (double h : half) share.push_back(std::pow(std::max(h / p.half_band, 0.25), -8.0 * gamma));
         WindowWeights t = w;   // equal shares: as the step was chosen
-        if (gamma > 0) window_design(X, share, xm, &t);
-        window_error(th, kPhase, xm, at, t, e2);
+        if (gamma > 0) window_design(values, share, &t);
+        window_error(turns, xm, at, t, e2);
         double worst = 0.0, sw = 0.0, ss = 0.0;
         for (int i = 0; i < 6; ++i) {
             for (int j = 0; j < kPhase; ++j) sw += count[i][j] * e2[j];
